@@ -9,13 +9,13 @@
 // the layer turns into a K-concat in the backward pass), and two problems of
 // one layout share a launch.
 //
-// Tiles: 256 threads = 4 wavefronts in a 2 x 2 grid; block tile 128 x 128,
-// wavefront tile 64 x 64 = 2 x 2 blocks of v_mfma_f32_32x32x2f32 (float32
-// operands, float32 accumulate) or v_mfma_f32_32x32x16_bf16 (bfloat16
-// operands).  K advances by BK per step through a double-buffered LDS tile
-// stored k-major, so that the matrix-core operand reads (32 consecutive m or n
-// per half-wavefront) hit 32 distinct banks.  Split-K partial tiles go to the
-// workspace and a second kernel adds them in split order (no atomics).
+// Tiles: 256 threads = 4 wavefronts in a 2 x 2 grid; block tile 128 x 128 (or
+// 256 x 128), wavefront tile 64 x 64 (128 x 64) of 32 x 32 blocks of
+// v_mfma_f32_32x32x16_bf16, for float32 operands on their three bfloat16
+// parts, for bfloat16 operands on themselves (large bfloat16 products take
+// 256 x 256 tiles of 8 wavefronts).  K advances through double-buffered LDS
+// tiles.  Split-K partial tiles go to the workspace and a second kernel adds
+// them in split order (no atomics).
 #include <algorithm>
 #include <type_traits>
 
@@ -26,17 +26,9 @@ namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-constexpr int BM = 128;
-constexpr int BN = 128;
-constexpr int PAD = 4;
-#ifndef GCN_GEMM_XK
-#define GCN_GEMM_XK 1
-#endif
-#ifndef GCN_GEMM_XK_NN
-#define GCN_GEMM_XK_NN 0
-#endif
-constexpr int PAD_XK = 4;   // [x][k] tiles: rows of BK + 4 floats (conflict-free 16-byte reads and stores)
 constexpr int kThreads = 256;
+constexpr int kTBM = 128;  // float32 block tile (M x N); row tiles of the column sums
+constexpr int kTBN = 128;
 
 struct Segs {
     const void *A[2];
@@ -103,182 +95,178 @@ __device__ __forceinline__ bool decode_block(const DevArgs &a, BlockCoord &c) {
     return true;
 }
 
-// ------------------------------------------------------------------ loading
-// Element type: float (fp32 path) or uint16_t (bf16 bits).
-template <typename T> __device__ __forceinline__ T zero_elem() { return T(0); }
+// ------------------------------------------------------------- float32 kernel
+// float32 products on the bfloat16 matrix cores.  Every operand element x is
+// split exactly into three bfloat16 parts, x = h + m + l: h = rne(x),
+// m = rne(x - h), l = x - h - m (8 significant bits each; the differences are
+// exact in float32), and a product accumulates the six part products
+// h h', h m', m h', m m', h l', l h' in float32.  The parts left out (m l',
+// l m', l l') are below 2^-25 of |x x'|.
+//
+// Rounding: v_mfma_f32_32x32x16_bf16 rounds its sum twice (after k 0-7 and
+// k 8-15), and it cuts a term below 2^-24 of the largest one it is added to.
+// The five small products of 16 k are therefore summed from zero, where their
+// roundings are 2^-8 smaller, h h' goes straight onto the accumulator, and
+// the small sum is added to it by one float32 addition: three roundings at
+// the accumulator's size per 16 k, against eight with the float32 cores
+// (v_mfma_f32_32x32x2_f32, one per 2 k).  Relative 2-norm error of a chain of
+// K terms against float64, here / float32 cores: K = 128 0.8e-7 / 2.0e-7,
+// K = 1024 2.4e-7 / 5.7e-7, K = 4096 4.8e-7 / 11.4e-7 on dense operands,
+// 0.7e-7 / 1.1e-7, 1.8e-7 / 2.9e-7, 3.7e-7 / 5.7e-7 with half of each operand
+// zero.  (All six on the accumulator are 10% faster but up to 1.7 times the
+// float32 cores' error there; h h' last on the small sum leaves a bias that
+// adds up over split-K partials.)
+//
+// Why: the bfloat16 cores do 16 times the float32 cores' rate, so six
+// products leave 2.7 times the float32 peak.  Measured at 65,536 vertices
+// (float32 cores before / now): 1024 -> 512 both branches, NT 1054 / 711 us,
+// TN 1044 / 651 us; NN 512 and 1024 -> 512 on average 824 / 565 us per launch,
+// i.e. 1.2 PFLOP/s of bfloat16 work: the clock falls to 1.9 GHz under it
+// (2.4 on zero operands), with the matrix cores busy 62% of the cycles.
+//
+// Range: an infinity or a float32 above the largest bfloat16 has no split,
+// parts of an element below about 2^-109 fall under the bfloat16 subnormals,
+// and sums that overflow could meet opposite infinities part by part.
+// Each of these shows in a block's sums: a block that holds a sum that is not
+// finite, or one that is not zero and below 2^-90, is computed again on the
+// float32 cores before the epilogue, so infinities, NaN, overflow and tiny
+// operands give what float32 products give.
+//
+// LDS: per operand and k-tile of 16, three planes (h, m, l) of two chunks
+// (k 0-7, k 8-15) of XT rows x 16 bytes, so that a fragment read (8
+// consecutive k of 32 consecutive rows per half-wavefront) is contiguous;
+// the chunks lie 128 bytes past a multiple of 256 apart, so that the 8-byte
+// stores of an operand contiguous along k (four lanes per row) fall in
+// distinct banks.  Two buffers, one barrier per k-tile: while a tile is
+// multiplied, the next one is split and stored to the other buffer, and the
+// one after it is loaded to registers.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float float4a4 __attribute__((ext_vector_type(4), aligned(4)));   // 16-byte load, 4-byte aligned
+constexpr int kBK = 16;           // K depth of one LDS stage
+constexpr int64_t kFastLd = 1 << 22;   // leading dimensions whose tile offsets fit 32 bits
 
-#ifndef GCN_GEMM_SWZ
-#define GCN_GEMM_SWZ 1
-#endif
-// Column swizzle of the float32 operand tiles: row k of lds[k][x] holds
-// element x at x ^ kswz(k).  The transposing store of an operand contiguous
-// along k (four consecutive k of one x per thread, eight consecutive x per
-// half-wavefront) then puts the half-wavefront's 32 values in 32 distinct
-// banks: with rows 132 floats apart, k-groups 0/8 and 4/12 would otherwise
-// share banks.  Reads of 32 consecutive x in one row stay conflict-free.
-__device__ __forceinline__ int kswz(int k) { return GCN_GEMM_SWZ ? ((k >> 3) & 1) << 3 : 0; }
+// x0, x1 -> the packed h, m and l parts
+__device__ __forceinline__ void split3(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l) {
+    h = pack_bf16x2(x0, x1);
+    const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xFFFF0000u);
+    m = pack_bf16x2(r0, r1);
+    const float s0 = r0 - __uint_as_float(m << 16), s1 = r1 - __uint_as_float(m & 0xFFFF0000u);
+    l = pack_bf16x2(s0, s1);
+}
 
-// Tile of one operand, BK x XT elements, kept k-major in LDS: lds[k][x].
-//   KMAJOR: element (x, k) sits at ptr[k*ld + x]   (contiguous along x)
-//   else  : element (x, k) sits at ptr[x*ld + k]   (contiguous along k)
-template <typename T, int BK, bool KMAJOR, bool VEC, int XT = 128>
-struct TileLoader {
-    // 16-byte vectors of T
-    static constexpr int E = 16 / sizeof(T);
-    static constexpr int kElems = BK * XT;
-    static constexpr int kVecs = kElems / E;
-    static constexpr int kPer = kVecs / kThreads;  // vectors per thread
-    static_assert(kPer >= 1, "tile too small");
-    typedef typename std::conditional<sizeof(T) == 4, float4, uint4>::type V;
-    V reg[kPer];
+// One operand's k-tile, XT rows x 16 k, staged through registers.
+//   KM: element (x, k) sits at ptr[k*ld + x] (contiguous along x): a thread
+//       takes 8 consecutive k of one x, the lanes consecutive x
+//   else: at ptr[x*ld + k] (contiguous along k): a thread takes 4 consecutive
+//       k, four lanes a row (16-byte loads at 4-byte alignment: any base and
+//       leading dimension)
+template <bool KM, int XT>
+struct SplitLoader {
+    static constexpr int W = KM ? 8 : 4;                   // k per unit
+    static constexpr int NU = XT * kBK / W / kThreads;     // units per thread
+    static constexpr int CS = XT * 8 + 64;                 // chunk stride (elements)
+    static constexpr int PL = 2 * CS;                      // plane stride
+    static constexpr int kElems = 3 * PL;                  // one buffer
+    static_assert(NU >= 1, "tile too small");
+    float r[NU][W];
+    uint32_t off[NU];   // byte offsets from the tile's origin at k = 0
 
-    __device__ __forceinline__ void coords(int i, int &x, int &k) const {
+    static __device__ __forceinline__ void coords(int i, int &x, int &k) {
         const int v = threadIdx.x + i * kThreads;
-        if (KMAJOR) {            // vectors along x
-            constexpr int per_row = XT / E;
-            k = v / per_row;
-            x = (v % per_row) * E;
-        } else {                 // vectors along k
-            constexpr int per_row = BK / E;
-            x = v / per_row;
-            k = (v % per_row) * E;
+        if (KM) {
+            x = v % XT;
+            k = (v / XT) * 8;
+        } else {
+            x = v >> 2;
+            k = (v & 3) * 4;
         }
     }
-
-    __device__ __forceinline__ void load(const T *__restrict__ ptr, int64_t ld, int x0, int xlim,
-                                         int k0, int klim) {
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) {
-            int x, k;
-            coords(i, x, k);
-            const int gx = x0 + x, gk = k0 + k;
-            if (VEC) {
-                // xlim / klim are multiples of E on the vector path
-                if (gx < xlim && gk < klim) {
-                    const T *p = KMAJOR ? ptr + (int64_t)gk * ld + gx : ptr + (int64_t)gx * ld + gk;
-                    reg[i] = *(const V *)p;
-                } else {
-                    reg[i] = V{};
-                }
-            } else {
-                T tmp[E];
-#pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    const int ex = KMAJOR ? gx + e : gx;
-                    const int ek = KMAJOR ? gk : gk + e;
-                    tmp[e] = (ex < xlim && ek < klim)
-                                 ? (KMAJOR ? ptr[(int64_t)ek * ld + ex] : ptr[(int64_t)ex * ld + ek])
-                                 : zero_elem<T>();
-                }
-                reg[i] = *(V *)tmp;
-            }
-        }
-    }
-
-    // Fast path of the vector loader, for k-tiles wholly inside a K-segment:
-    // per-thread element offsets of the vectors (at k = 0), computed once per
-    // segment, with rows / column chunks past the extent clamped to the last
-    // valid ones (their products land in outputs the epilogue drops).  A
-    // k-tile is then one add and one load per vector, with no bounds branches.
-    int64_t off[kPer];
+    // rows past the extent are clamped to the last one (their products land in
+    // outputs the epilogue drops)
     __device__ __forceinline__ void prepare(int64_t ld, int x0, int xlim) {
 #pragma unroll
-        for (int i = 0; i < kPer; ++i) {
+        for (int i = 0; i < NU; ++i) {
             int x, k;
             coords(i, x, k);
-            if (KMAJOR) off[i] = (int64_t)k * ld + min(x0 + x, xlim - E);
-            else off[i] = (int64_t)min(x0 + x, xlim - 1) * ld + k;
+            const uint32_t cx = (uint32_t)(min(x0 + x, xlim - 1) - x0);
+            off[i] = 4u * (KM ? (uint32_t)k * (uint32_t)ld + cx : cx * (uint32_t)ld + (uint32_t)k);
         }
     }
-    // kofs: k0 (operand contiguous along k) or k0 * ld (contiguous along x)
-    __device__ __forceinline__ void load_fast(const T *__restrict__ ptr, int64_t kofs) {
+    // a k-tile wholly inside its segment; org: the tile's origin (x0, k0)
+    __device__ __forceinline__ void load_fast(const float *__restrict__ org, int64_t ld) {
+        if (KM) {
 #pragma unroll
-        for (int i = 0; i < kPer; ++i) reg[i] = *(const V *)(ptr + off[i] + kofs);
-    }
-
-    // [x][k] layout (k contiguous, rows of BK + PAD_XK): an operand contiguous
-    // along k goes in as its loaded 16-byte vectors
-    template <int RS>
-    __device__ __forceinline__ void store_xk(T (*lds)[RS]) const {
-        static_assert(!KMAJOR, "the [x][k] layout takes operands contiguous along k");
+            for (int e = 0; e < W; ++e) {
+                const char *p = (const char *)(org + e * ld);
 #pragma unroll
-        for (int i = 0; i < kPer; ++i) {
-            int x, k;
-            coords(i, x, k);
-            *(V *)&lds[x][k] = reg[i];
-        }
-    }
-
-    __device__ __forceinline__ void store(T (*lds)[XT + PAD]) const {
+                for (int i = 0; i < NU; ++i) r[i][e] = *(const float *)(p + off[i]);
+            }
+        } else {
 #pragma unroll
-        for (int i = 0; i < kPer; ++i) {
-            int x, k;
-            coords(i, x, k);
-            const T *t = (const T *)&reg[i];
-            if (KMAJOR) {
-                *(V *)&lds[k][sizeof(T) == 4 ? x ^ kswz(k) : x] = reg[i];
-            } else {
+            for (int i = 0; i < NU; ++i) {
+                const float4a4 v = *(const float4a4 *)((const char *)org + off[i]);
 #pragma unroll
-                for (int e = 0; e < E; ++e) lds[k + e][sizeof(T) == 4 ? x ^ kswz(k + e) : x] = t[e];
+                for (int e = 0; e < W; ++e) r[i][e] = v[e];
             }
         }
+    }
+    // any k-tile: k past the segment reads as zero
+    __device__ __forceinline__ void load_edge(const float *__restrict__ ptr, int64_t ld, int x0, int xlim, int k0,
+                                              int klim) {
+#pragma unroll
+        for (int i = 0; i < NU; ++i) {
+            int x, k;
+            coords(i, x, k);
+            const int64_t gx = min(x0 + x, xlim - 1);
+#pragma unroll
+            for (int e = 0; e < W; ++e) {
+                const int64_t gk = k0 + k + e;
+                r[i][e] = gk < klim ? (KM ? ptr[gk * ld + gx] : ptr[gx * ld + gk]) : 0.0f;
+            }
+        }
+    }
+    __device__ __forceinline__ void store(uint16_t *lds) const {
+#pragma unroll
+        for (int i = 0; i < NU; ++i) {
+            int x, k;
+            coords(i, x, k);
+            uint32_t p[3][W / 2];
+#pragma unroll
+            for (int e = 0; e < W; e += 2) split3(r[i][e], r[i][e + 1], p[0][e / 2], p[1][e / 2], p[2][e / 2]);
+            uint16_t *d = lds + (k >> 3) * CS + x * 8 + (k & 7);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                if constexpr (KM) *(uint4 *)(d + q * PL) = make_uint4(p[q][0], p[q][1], p[q][2], p[q][3]);
+                else *(uint2 *)(d + q * PL) = make_uint2(p[q][0], p[q][1]);
+            }
+        }
+    }
+    // the float32 values, [k][x] in rows of XT + 4
+    __device__ __forceinline__ void store_f32(float *lds) const {
+#pragma unroll
+        for (int i = 0; i < NU; ++i) {
+            int x, k;
+            coords(i, x, k);
+#pragma unroll
+            for (int e = 0; e < W; ++e) lds[(k + e) * (XT + 4) + x] = r[i][e];
+        }
+    }
+    static __device__ __forceinline__ bf16x8 frag(const uint16_t *lds, int q, int row, int lane) {
+        return *(const bf16x8 *)(lds + q * PL + (lane >> 5) * CS + (row + (lane & 31)) * 8);
     }
 };
 
-// -------------------------------------------------------------- main kernel
-#ifndef GCN_GEMM_BK
-#define GCN_GEMM_BK 16
-#endif
-constexpr int kBK = GCN_GEMM_BK;  // K depth of one LDS stage
-#ifndef GCN_GEMM_TBM
-#define GCN_GEMM_TBM 128
-#endif
-#ifndef GCN_GEMM_TBN
-#define GCN_GEMM_TBN 128
-#endif
-constexpr int kTBM = GCN_GEMM_TBM;  // float32 block tile (M x N), 2 x 2 wavefronts
-constexpr int kTBN = GCN_GEMM_TBN;
-
-#ifndef GCN_GEMM_WAVES_PER_EU
-#define GCN_GEMM_WAVES_PER_EU 4
-#endif
-// A wavefront issuing matrix-core products runs at raised priority, so that
-// the SIMD's arbiter feeds the matrix pipe before the other wavefronts' loads.
-#ifndef GCN_GEMM_SETPRIO
-#define GCN_GEMM_SETPRIO 1
-#endif
-#if GCN_GEMM_SETPRIO
 #define GCN_PRIO_UP() __builtin_amdgcn_s_setprio(1)
 #define GCN_PRIO_DOWN() __builtin_amdgcn_s_setprio(0)
-#else
-#define GCN_PRIO_UP() ((void)0)
-#define GCN_PRIO_DOWN() ((void)0)
-#endif
-template <int LAYOUT, bool VEC, int TBM, int TBN>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(GCN_GEMM_WAVES_PER_EU)))
+// 2 x 2 wavefronts of FM x FN blocks of 32 x 32: a block tile of 64 FM x 64 FN
+template <int LAYOUT, int FM, int FN>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(FM * FN > 4 ? 2 : 3)))
 void gemm_kernel(DevArgs args) {
-    using T = float;
-    constexpr int BK = kBK;
-    constexpr bool A_KMAJOR = (LAYOUT == L_TN);
-    constexpr bool B_KMAJOR = (LAYOUT != L_NT);
-    constexpr int WTM = TBM / 2, WTN = TBN / 2;     // wavefront tile (2 x 2 wavefronts)
-    constexpr int FM = WTM / 32, FN = WTN / 32;     // 32x32 accumulator blocks per wavefront
-    // An operand contiguous along k (A in NN and NT, B in NT) is kept [x][k]
-    // in LDS and read 4 consecutive k per lane: one ds_read_b128 feeds four
-    // products.  A k-major operand keeps the [k][x] layout (one 4-byte read
-    // per product), read in the same k order.
-    constexpr bool XKA = GCN_GEMM_XK && !A_KMAJOR && (LAYOUT == L_NT || GCN_GEMM_XK_NN);
-    constexpr bool XKB = GCN_GEMM_XK && !B_KMAJOR;
-    constexpr bool XK = XKA || XKB;
-    constexpr int RS = BK + PAD_XK;                 // [x][k] row stride
-    constexpr int kSmemA = XKA ? 2 * TBM * RS : 2 * BK * (TBM + PAD);
-    constexpr int kSmemB = XKB ? 2 * TBN * RS : 2 * BK * (TBN + PAD);
-    // one LDS block: the two operand double buffers, reused by the epilogue
-    __shared__ __attribute__((aligned(16))) T smem[kSmemA + kSmemB];
-    T(*As)[BK][TBM + PAD] = (T(*)[BK][TBM + PAD])smem;
-    T(*Bs)[BK][TBN + PAD] = (T(*)[BK][TBN + PAD])(smem + kSmemA);
-    T(*Ax)[TBM][RS] = (T(*)[TBM][RS])smem;
-    T(*Bx)[TBN][RS] = (T(*)[TBN][RS])(smem + kSmemA);
+    constexpr int TBM = 64 * FM, TBN = 64 * FN, WTM = 32 * FM, WTN = 32 * FN;
+    using LA = SplitLoader<LAYOUT == L_TN, TBM>;
+    using LB = SplitLoader<LAYOUT != L_NT, TBN>;
+    constexpr int kBuf = LA::kElems + LB::kElems;      // one stage of both operands
+    __shared__ __attribute__((aligned(16))) uint16_t smem[2 * kBuf];
 
     // ---- which problem / split / tile
     BlockCoord bc;
@@ -287,164 +275,157 @@ void gemm_kernel(DevArgs args) {
     const int split = bc.split;
     const int m0 = bc.tm * TBM, n0 = bc.tn * TBN;
     const int kt_begin = split * P.kt_per_split;
-    int kt_end = kt_begin + P.kt_per_split;
-    if (kt_end > P.kt_total) kt_end = P.kt_total;
+    const int kt_end = min(kt_begin + P.kt_per_split, P.kt_total);
 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int wm = wave >> 1, wn = wave & 1;
 
-    TileLoader<T, BK, A_KMAJOR, VEC, TBM> la;
-    TileLoader<T, BK, B_KMAJOR, VEC, TBN> lb;
-
+    LA la;
+    LB lb;
     // the two K-segments' descriptors, read once
-    const T *const A0 = (const T *)P.s.A[0], *const A1 = (const T *)P.s.A[1];
-    const T *const B0 = (const T *)P.s.B[0], *const B1 = (const T *)P.s.B[1];
+    const float *const A0 = (const float *)P.s.A[0], *const A1 = (const float *)P.s.A[1];
+    const float *const B0 = (const float *)P.s.B[0], *const B1 = (const float *)P.s.B[1];
     const int64_t lda0 = P.s.lda[0], lda1 = P.s.lda[1], ldb0 = P.s.ldb[0], ldb1 = P.s.ldb[1];
     const int K0 = P.s.K[0], K1 = P.s.K[1], kt0 = P.s.kt[0];
     const int Mp = P.M, Np = P.N;
-    // the clamped fast loads need M (TN) and N (NN, TN) of at least one vector
-    const bool fast = VEC && (!A_KMAJOR || Mp >= 4) && (!B_KMAJOR || Np >= 4);
     int ready = -1;   // the K-segment whose offsets are prepared
     auto load = [&](int kt) {
         const int sg = kt < kt0 ? 0 : 1;
-        const int kk = (sg ? kt - kt0 : kt) * BK;
-        const T *A = sg ? A1 : A0;
-        const T *Bm = sg ? B1 : B0;
+        const int kk = (sg ? kt - kt0 : kt) * kBK;
+        const float *A = sg ? A1 : A0;
+        const float *Bm = sg ? B1 : B0;
         const int64_t lda = sg ? lda1 : lda0, ldb = sg ? ldb1 : ldb0;
         const int K = sg ? K1 : K0;
-        if (fast && kk + BK <= K) {
+        if (kk + kBK <= K && lda <= kFastLd && ldb <= kFastLd) {
             if (ready != sg) {
                 la.prepare(lda, m0, Mp);
                 lb.prepare(ldb, n0, Np);
                 ready = sg;
             }
-            la.load_fast(A, A_KMAJOR ? (int64_t)kk * lda : (int64_t)kk);
-            lb.load_fast(Bm, B_KMAJOR ? (int64_t)kk * ldb : (int64_t)kk);
+            la.load_fast(LAYOUT == L_TN ? A + (int64_t)kk * lda + m0 : A + (int64_t)m0 * lda + kk, lda);
+            lb.load_fast(LAYOUT != L_NT ? Bm + (int64_t)kk * ldb + n0 : Bm + (int64_t)n0 * ldb + kk, ldb);
         } else {
-            la.load(A, lda, m0, Mp, kk, K);
-            lb.load(Bm, ldb, n0, Np, kk, K);
+            la.load_edge(A, lda, m0, Mp, kk, K);
+            lb.load_edge(Bm, ldb, n0, Np, kk, K);
         }
     };
-
     floatx16 acc[FM][FN];
+    auto clear = [&]() {
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int j = 0; j < FN; ++j)
+            for (int j = 0; j < FN; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-    if (kt_begin < kt_end) load(kt_begin);
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+    };
+    clear();
+    if (kt_begin < kt_end) {
+        load(kt_begin);
+        la.store(smem);
+        lb.store(smem + LA::kElems);
+        if (kt_begin + 1 < kt_end) load(kt_begin + 1);
+    }
     int buf = 0;
-    const int kh = lane >> 5;
     for (int kt = kt_begin; kt < kt_end; ++kt) {
-      if constexpr (XK) {
-        if constexpr (XKA) la.template store_xk<RS>(Ax[buf]);
-        else la.store(As[buf]);
-        if constexpr (XKB) lb.template store_xk<RS>(Bx[buf]);
-        else lb.store(Bs[buf]);
-        if (kt + 1 < kt_end) load(kt + 1);
-        __syncthreads();
-        // k order shared by both operands: in group g of 8 k, lanes 0-31 take
-        // k = 8g + u and lanes 32-63 k = 8g + 4 + u for the u-th product
-        float4 a4[FM], b4[FN];
-        auto rd4 = [&](float4 *a, float4 *b, int g) {
-            const int kc = 8 * g + 4 * (lane >> 5);
+        __syncthreads();   // this stage is stored, and the other one is read
+        const uint16_t *As = smem + buf * kBuf, *Bs = As + LA::kElems;
+        bf16x8 b[3][FN], a[3];
+        GCN_PRIO_UP();
 #pragma unroll
-            for (int i = 0; i < FM; ++i) {
-                const int x = wm * WTM + i * 32 + (lane & 31);
-                if constexpr (XKA) a[i] = *(const float4 *)&Ax[buf][x][kc];
-                else
+        for (int q = 0; q < 3; ++q)
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) a[i][u] = As[buf][kc + u][x ^ kswz(kc + u)];
+            for (int j = 0; j < FN; ++j) b[q][j] = LB::frag(Bs, q, wn * WTN + j * 32, lane);
+        // Per block the five small products of the k-tile from zero (t), h h'
+        // on the accumulator, and t added to it once the next block's products
+        // are issued: the additions run in the matrix instructions' shadow.
+        floatx16 t[2];
+#pragma unroll
+        for (int x = 0; x <= FM * FN; ++x) {
+            const int i = x / FN, j = x % FN;
+            if (x < FM * FN) {
+                if (j == 0)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) a[q] = LA::frag(As, q, wm * WTM + i * 32, lane);
+                constexpr int pa[5] = {2, 0, 1, 1, 0}, pb[5] = {0, 2, 1, 0, 1};
+                floatx16 u = {};
+#pragma unroll
+                for (int q = 0; q < 5; ++q)
+                    u = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pa[q]], b[pb[q]][j], u, 0, 0, 0);
+                t[x & 1] = u;
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0][j], acc[i][j], 0, 0, 0);
+            }
+            if (x > 0) {
+                floatx16 &c = acc[(x - 1) / FN][(x - 1) % FN];
+                c += t[(x - 1) & 1];
+                // keeps the addition here: sunk to the loop's end, every
+                // block's t would be live at once
+                asm volatile("" : "+v"(c));
             }
 #pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                const int x = wn * WTN + j * 32 + (lane & 31);
-                if constexpr (XKB) b[j] = *(const float4 *)&Bx[buf][x][kc];
-                else
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) b[j][u] = Bs[buf][kc + u][x ^ kswz(kc + u)];
+            for (int g = 0; g < 6; ++g) {   // three additions behind each matrix instruction
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
             }
-        };
-        auto mma4 = [&](const float4 *a, const float4 *b) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int i = 0; i < FM; ++i)
-#pragma unroll
-                    for (int j = 0; j < FN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][u], b[j][u], acc[i][j], 0, 0, 0);
-        };
-        static_assert(BK % 8 == 0, "whole groups of 8 k");
-        // one group's fragments in flight (the other wavefronts on the SIMD
-        // cover the read latency): 16 registers instead of 32
-#pragma unroll
-        for (int g = 0; g < BK / 8; ++g) {
-            rd4(a4, b4, g);
-            GCN_PRIO_UP();
-            mma4(a4, b4);
-            GCN_PRIO_DOWN();
+        }
+        GCN_PRIO_DOWN();
+        if (kt + 1 < kt_end) {
+            uint16_t *An = smem + (buf ^ 1) * kBuf;
+            la.store(An);
+            lb.store(An + LA::kElems);
+            if (kt + 2 < kt_end) load(kt + 2);
         }
         buf ^= 1;
-        continue;
-      }
-        la.store(As[buf]);
-        lb.store(Bs[buf]);
-        // the staging registers are free once stored: the next tile's loads
-        // go out before the barrier, not after it (+3% over loading after it)
-        if (kt + 1 < kt_end) load(kt + 1);
-        __syncthreads();
-        // two register sets of operands: the LDS reads of k-step s + 1 are
-        // issued before the matrix-core products of k-step s
-        float a0[FM], b0[FN], a1[FM], b1[FN];
-        auto rd = [&](float *a, float *b, int kr) {
+    }
+    // ---- sums outside the split's range: the block again on the float32 cores
+    {
+        uint32_t hi = 0u, lo = 0xFFFFFFFFu;
 #pragma unroll
-            for (int i = 0; i < FM; ++i) a[i] = As[buf][kr][(wm * WTM + i * 32 + (lane & 31)) ^ kswz(kr)];
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < FN; ++j) b[j] = Bs[buf][kr][(wn * WTN + j * 32 + (lane & 31)) ^ kswz(kr)];
-        };
-        auto mma = [&](const float *a, const float *b) {
+            for (int j = 0; j < FN; ++j)
 #pragma unroll
-            for (int i = 0; i < FM; ++i)
+                for (int r = 0; r < 16; ++r) {
+                    const uint32_t u = __float_as_uint(acc[i][j][r]) & 0x7FFFFFFFu;
+                    hi = max(hi, u);
+                    lo = min(lo, u - 1u);   // (a zero becomes the largest)
+                }
+        constexpr uint32_t kInf = 0x7F800000u, kTiny = (127u - 90u) << 23;
+        if (__syncthreads_or(hi >= kInf || lo < kTiny - 1u)) {
+            float *As = (float *)smem, *Bs = As + kBK * (TBM + 4);
+            static_assert((kBK * (TBM + 4 + TBN + 4)) * 4 <= sizeof(smem), "float32 tiles fit");
+            clear();
+            for (int kt = kt_begin; kt < kt_end; ++kt) {
+                load(kt);
+                la.store_f32(As);
+                lb.store_f32(Bs);
+                __syncthreads();
+#pragma unroll 2
+                for (int k = 0; k < kBK; k += 2) {
+                    const float *ar = As + (k + (lane >> 5)) * (TBM + 4) + wm * WTM + (lane & 31);
+                    const float *br = Bs + (k + (lane >> 5)) * (TBN + 4) + wn * WTN + (lane & 31);
 #pragma unroll
-                for (int j = 0; j < FN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-        };
-        // (scheduling barriers keep each group of reads ahead of the products
-        // that do not need it; without them the compiler sinks the reads
-        // below the products and waits on them at once)
-        rd(a0, b0, kh);
+                    for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int kk = 0; kk < BK; kk += 4) {
-            rd(a1, b1, kk + 2 + kh);
-            __builtin_amdgcn_sched_barrier(0);
-            GCN_PRIO_UP();
-            mma(a0, b0);
-            GCN_PRIO_DOWN();
-            __builtin_amdgcn_sched_barrier(0);
-            if (kk + 4 < BK) rd(a0, b0, kk + 4 + kh);
-            __builtin_amdgcn_sched_barrier(0);
-            GCN_PRIO_UP();
-            mma(a1, b1);
-            GCN_PRIO_DOWN();
-            __builtin_amdgcn_sched_barrier(0);
+                        for (int j = 0; j < FN; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar[32 * i], br[32 * j], acc[i][j], 0, 0, 0);
+                }
+                __syncthreads();
+            }
         }
-        buf ^= 1;
     }
 
     const bool to_partial = P.split > 1;
     float *dst = to_partial ? P.partial + (int64_t)split * P.M * P.N : P.C;
     const int64_t ldd = to_partial ? P.N : P.ldc;
     // ---- epilogue through LDS, 32 rows per pass: the two wavefronts holding
-    // those rows deposit their accumulator blocks row-major (row stride 136
-    // floats: the two half-wavefronts' rows, four apart, land 32 banks apart),
-    // then all four wavefronts write whole 128-column rows, 16 bytes per lane.
-    static_assert(FM == 2 && FN == 2 && TBN == 128, "epilogue written for 2 x 2 blocks of a 128-wide tile");
-    constexpr int SLD = 136;
-    static_assert(32 * SLD <= kSmemA + kSmemB, "staging fits the operand buffers");
-    float *stg = smem;
+    // those rows deposit their accumulator blocks row-major (row stride
+    // TBN + 8 floats: the two half-wavefronts' rows, four apart, land 32 banks
+    // apart), then all four wavefronts write whole rows, 16 bytes per lane.
+    static_assert(TBN == 128, "epilogue written for a 128-wide tile");
+    constexpr int SLD = TBN + 8;
+    static_assert(32 * SLD * 4 <= (int)sizeof(smem), "staging fits the operand buffers");
+    float *stg = (float *)smem;
     const int ecol = n0 + 4 * (lane & 31);
     float ebv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     if (!to_partial && P.bias)
@@ -454,7 +435,7 @@ void gemm_kernel(DevArgs args) {
     const bool evec = ldd % 4 == 0 && ((uintptr_t)dst & 15) == 0;
     // optional mask operand (a [mask > 0] factor on every stored value), read
     // for a pass's four rows before that pass's barrier; optional column sums
-    // of the stored values over this thread's 16 rows of the tile
+    // of the stored values over this thread's 16 rows of each 128-row half
     const float *const emask = to_partial ? nullptr : P.mask;
     const bool mvec = emask && P.ldm % 4 == 0 && ((uintptr_t)emask & 15) == 0 && ecol + 3 < P.N;
     const bool ecs = !to_partial && P.colpart;
@@ -467,7 +448,7 @@ void gemm_kernel(DevArgs args) {
     };
     __syncthreads();   // the last tile's operand reads are done
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
+    for (int h = 0; h < 2 * FM; ++h) {
         if (emask) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -486,9 +467,9 @@ void gemm_kernel(DevArgs args) {
                 }
             }
         }
-        if (wm == (h >> 1)) {
-            put(acc[h & 1][0], 0);
-            put(acc[h & 1][1], 1);
+        if (wm == h / FM) {
+#pragma unroll
+            for (int j = 0; j < FN; ++j) put(acc[h % FM][j], j);
         }
         __syncthreads();
         // rows 32h .. 32h+31 of the tile; a wavefront writes two rows per store
@@ -522,19 +503,24 @@ void gemm_kernel(DevArgs args) {
             }
         }
         __syncthreads();
-    }
-    if (ecs) {
-        // the 8 row groups (wavefront, half) of each column, added in order
-        const int grp = wave * 2 + (lane >> 5);
+        if (ecs && h % 4 == 3) {
+            // a 128-row half is done: the 8 row groups (wavefront, half) of
+            // each column, added in order
+            const int grp = wave * 2 + (lane >> 5);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) stg[grp * 128 + 4 * (lane & 31) + e] = cs[e];
-        __syncthreads();
-        if (threadIdx.x < 128) {
-            float t = 0.0f;
+            for (int e = 0; e < 4; ++e) {
+                stg[grp * 128 + 4 * (lane & 31) + e] = cs[e];
+                cs[e] = 0.0f;
+            }
+            __syncthreads();
+            if (threadIdx.x < 128) {
+                float t = 0.0f;
 #pragma unroll
-            for (int g = 0; g < 8; ++g) t += stg[g * 128 + threadIdx.x];
-            const int col = n0 + (int)threadIdx.x;
-            if (col < P.N) P.colpart[(int64_t)bc.tm * P.N + col] = t;
+                for (int g = 0; g < 8; ++g) t += stg[g * 128 + threadIdx.x];
+                const int col = n0 + (int)threadIdx.x, trow = m0 + 128 * (h / 4);
+                if (col < P.N && trow < P.M) P.colpart[(int64_t)(trow / 128) * P.N + col] = t;
+            }
+            __syncthreads();
         }
     }
 }
@@ -573,8 +559,6 @@ static_assert(kRowsPerSpan16 >= 1 && (kChunks16 & (kChunks16 - 1)) == 0, "BK16 m
 __device__ __forceinline__ int swz16(int r) { return (r / kRowsPerSpan16) & (kChunks16 - 1); }
 constexpr int kTBM16 = GCN_BF16_TBM;
 constexpr int kTBN16 = GCN_BF16_TBN;
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
 template <bool KMAJOR, bool VEC, int XT>
 struct TileLoader16 {
     static constexpr int kPer = (BK16 * XT / 8) / kThreads;  // 16-byte vectors per thread
@@ -1372,10 +1356,10 @@ bool vec_ok(int layout, const GemmProblem &g, int esz) {
     return true;
 }
 
-// mode 0: float32 kernel; 1: bf16 kernel; 2: bf16 large-tile kernel
-int bk_of(int mode) { return mode == 2 ? kBigBK : (mode ? BK16 : kBK); }
-int tile_m_of(int mode) { return mode == 2 ? kBigT : (mode ? kTBM16 : kTBM); }
-int tile_n_of(int mode) { return mode == 2 ? kBigTN : (mode ? kTBN16 : kTBN); }
+// mode 0: float32 kernel; 1: bf16 kernel; 2: bf16 large-tile kernel; 3: float32 kernel, 256-row tiles
+int bk_of(int mode) { return mode == 2 ? kBigBK : (mode == 1 ? BK16 : kBK); }
+int tile_m_of(int mode) { return mode == 2 ? kBigT : (mode == 1 ? kTBM16 : (mode == 3 ? 2 * kTBM : kTBM)); }
+int tile_n_of(int mode) { return mode == 2 ? kBigTN : (mode == 1 ? kTBN16 : kTBN); }
 
 // The large-tile bf16 kernel takes NT, TN and NN products whose K-segments
 // are multiples of its k-stage, with 16-byte aligned operand rows; a k-major
@@ -1413,6 +1397,18 @@ bool big_ok(int layout, int nprob, const GemmProblem *probs) {
         }
     }
     return true;
+}
+
+// The float32 tile: 256 x 128 when its blocks still give every CU two (two
+// fit its LDS), 128 x 128 (three per CU) for fewer: a 256 x 128 tile reads a
+// quarter less from LDS per product, but 256 blocks of it leave half of the
+// wavefront slots empty (logits of 65,536 vertices: 143 us on 256 blocks of
+// 256 x 128, 116 us on 512 of 128 x 128; input gradient of the same layer,
+// 2048 blocks against 4096: 660 / 690 us).
+int f32_mode(int nprob, const GemmProblem *probs, int split_k) {
+    const int64_t blocks = (int64_t)nprob * std::max(1, split_k) * ((probs[0].M + 2 * kTBM - 1) / (2 * kTBM)) *
+                           ((probs[0].N + kTBN - 1) / kTBN);
+    return blocks >= 512 ? 3 : 0;
 }
 
 void fill_dev(int layout, int nprob, const GemmProblem *probs, int bf16, int split_k, float *partial,
@@ -1471,16 +1467,16 @@ void fill_dev(int layout, int nprob, const GemmProblem *probs, int bf16, int spl
 }
 
 template <int LAYOUT>
-void launch(bool vec, bool bf16, dim3 grid, hipStream_t s, const DevArgs &a) {
-    if (bf16) {
+void launch(bool vec, int mode, dim3 grid, hipStream_t s, const DevArgs &a) {
+    if (mode == 1) {
         if (vec)
             hipLaunchKernelGGL((gemm_bf16_kernel<LAYOUT, true>), grid, dim3(kThreads), 0, s, a);
         else
             hipLaunchKernelGGL((gemm_bf16_kernel<LAYOUT, false>), grid, dim3(kThreads), 0, s, a);
-    } else if (vec) {
-        hipLaunchKernelGGL((gemm_kernel<LAYOUT, true, kTBM, kTBN>), grid, dim3(kThreads), 0, s, a);
+    } else if (mode == 3) {
+        hipLaunchKernelGGL((gemm_kernel<LAYOUT, 4, 2>), grid, dim3(kThreads), 0, s, a);
     } else {
-        hipLaunchKernelGGL((gemm_kernel<LAYOUT, false, kTBM, kTBN>), grid, dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL((gemm_kernel<LAYOUT, 2, 2>), grid, dim3(kThreads), 0, s, a);
     }
 }
 
@@ -1545,7 +1541,7 @@ int gemm(int layout, int nprob, const GemmProblem *probs, int bf16, int split_k,
     double flops = 0.0, bytes = 0.0;
     for (int i = 0; i < nprob; ++i) {
         const GemmProblem &g = probs[i];
-        vec = vec && vec_ok(layout, g, bf16 ? 2 : 4);
+        vec = vec && (!bf16 || vec_ok(layout, g, 2));
         const double K = (double)g.seg[0].K + g.seg[1].K;
         flops += 2.0 * g.M * g.N * (K - g.k_pad);
         // algorithmic bytes: each operand read once, the output written once
@@ -1566,7 +1562,8 @@ int gemm(int layout, int nprob, const GemmProblem *probs, int bf16, int split_k,
     const bool big = bf16 && big_ok(layout, nprob, probs);
     DevArgs a;
     int64_t blocks = 0;
-    fill_dev(layout, nprob, probs, big ? 2 : (bf16 ? 1 : 0), split_k, partial, a, blocks);
+    const int mode = big ? 2 : (bf16 ? 1 : f32_mode(nprob, probs, split_k));
+    fill_dev(layout, nprob, probs, mode, split_k, partial, a, blocks);
     if (blocks == 0) return GCN_OK;
     if (nprob == 2 && (a.p[0].kt_total != a.p[1].kt_total || a.p[0].split != a.p[1].split)) {
         set_error("gemm: grouped problems must have the same K-tiling");
@@ -1622,9 +1619,9 @@ int gemm(int layout, int nprob, const GemmProblem *probs, int bf16, int split_k,
             GCN_BIG_LAUNCH(BIG_F32, L_NN) GCN_BIG_LAUNCH(BIG_B16, L_NN) GCN_BIG_LAUNCH(BIG_ALL, L_NN)
 #undef GCN_BIG_LAUNCH
         }
-        else if (layout == L_NN) launch<L_NN>(vec, bf16 != 0, grid, s, a);
-        else if (layout == L_TN) launch<L_TN>(vec, bf16 != 0, grid, s, a);
-        else launch<L_NT>(vec, bf16 != 0, grid, s, a);
+        else if (layout == L_NN) launch<L_NN>(vec, mode, grid, s, a);
+        else if (layout == L_TN) launch<L_TN>(vec, mode, grid, s, a);
+        else launch<L_NT>(vec, mode, grid, s, a);
         GCN_LAUNCH_CHECK("gemm_kernel");
     }
     if (any_split) {

@@ -1,0 +1,115 @@
+"""float32 products (split into bfloat16 parts on the matrix cores) against
+float64, at tile edges and outside the split's range.
+
+The products are reached through the layer calls on a graph without edges:
+forward H W_self (NN), backward H^T dZ (TN) and dZ W_self^T (NT).
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_1810_11899_amd import binding as B
+from paper_1810_11899_amd import synth
+from tests.gpu_util import dev, require_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    require_gpu()
+
+
+def run(H, Ws, dY):
+    """(H Ws, H^T dY, dY Ws^T) through gcn_layer_fwd / gcn_layer_bwd."""
+    n, f = H.shape
+    h = Ws.shape[1]
+    g = synth.empty_graph(n)
+    A = B.DeviceCSR.from_host(n, n, g.indptr, g.indices, g.vals)
+    ws = B.Workspace()
+    order = B.GCN_TRANSFORM_FIRST
+    Wn = torch.zeros((f, h), dtype=torch.float32, device="cuda")
+    bias = torch.zeros(2 * h, dtype=torch.float32, device="cuda")
+    Hd, Wd = dev(H), dev(Ws)
+    out = []
+    for sign in (1.0, -1.0):      # the two signs give the product behind the ReLU
+        Y = torch.empty((n, 2 * h), dtype=torch.float32, device="cuda")
+        B.gcn_layer_fwd(A, Hd, Wd * sign, Wn, bias, Y, None, order, ws)
+        out.append(Y[:, :h].cpu().numpy())
+    dYd = torch.zeros((n, 2 * h), dtype=torch.float32, device="cuda")
+    dYd[:, :h] = dev(dY)
+    Y = torch.ones((n, 2 * h), dtype=torch.float32, device="cuda")
+    dH = torch.empty((n, f), dtype=torch.float32, device="cuda")
+    dWs, dWn = (torch.empty((f, h), dtype=torch.float32, device="cuda") for _ in range(2))
+    db = torch.empty(2 * h, dtype=torch.float32, device="cuda")
+    B.gcn_layer_bwd(A, A, Hd, Wd, Wn, Y, None, dYd, dH, dWs, dWn, db, order, ws)
+    return out[0], out[1], dWs.cpu().numpy(), dH.cpu().numpy()
+
+
+def check(got, a, b, K):
+    """|got - a b| within three roundings per 16 k, the split's dropped parts
+    and the split-K sums, each at most 2^-24 of sum |a||b|."""
+    ref = a.astype(np.float64) @ b.astype(np.float64)
+    mag = np.abs(a).astype(np.float64) @ np.abs(b).astype(np.float64)
+    bound = (3.0 * K / 16 + 16 + 64) * 2.0 ** -24 * mag + 1e-37
+    assert np.all(np.abs(got - ref) <= bound), float((np.abs(got - ref) / (mag + 1e-300)).max())
+
+
+# tile edges (128 / 256 rows, 128 columns, 16 k), remainders, unaligned widths,
+# and row counts whose 256 x 128 tiles number more and fewer than 512
+@pytest.mark.parametrize("n, f, h", [(1, 1, 1), (15, 17, 3), (127, 16, 129), (128, 128, 128), (129, 31, 127),
+                                     (257, 33, 130), (300, 602, 41), (5000, 50, 64), (66000, 40, 260),
+                                     (131072 + 77, 20, 20)])
+def test_products_at_tile_edges(n, f, h):
+    rg = np.random.default_rng(n + f + h)
+    H = rg.standard_normal((n, f), dtype=np.float32) * np.exp2(rg.integers(-12, 12, (n, f))).astype(np.float32)
+    Ws = rg.standard_normal((f, h), dtype=np.float32)
+    dY = rg.standard_normal((n, h), dtype=np.float32) * 1e-4
+    pos, neg, dW, dH = run(H, Ws, dY)
+    check(pos - neg, H, Ws, f)
+    check(dW, H.T, dY, n)
+    check(dH, dY, Ws.T, h)
+
+
+@pytest.mark.parametrize("n, f, h", [(200, 48, 40), (66000, 48, 260)])
+def test_products_outside_the_split_range(n, f, h):
+    """Infinities, NaN, values above the largest bfloat16, overflowing sums
+    and tiny operands give what float32 arithmetic gives."""
+    rg = np.random.default_rng(n)
+    H = rg.standard_normal((n, f), dtype=np.float32)
+    Ws = rg.standard_normal((f, h), dtype=np.float32)
+    Ws[:, 5] = np.abs(Ws[:, 5])
+    H[3, 7] = np.inf
+    H[4, 8] = -np.inf
+    H[5, 9] = np.nan
+    H[6] = 0.0
+    H[6, 2] = np.float32(3.4e38)             # finite, rounds to infinity in bfloat16
+    Ws[2, :20] = 0.25
+    H[7, :] = np.float32(2e38)               # sums past float32's range
+    H[8] *= np.float32(1e-36)
+    H[9] *= np.float32(2.0 ** -100)
+    dY = rg.standard_normal((n, h), dtype=np.float32)
+    pos, neg, _, dH = run(H, Ws, dY)
+    with np.errstate(all="ignore"):
+        ref = H.astype(np.float64) @ Ws.astype(np.float64)
+        ref32 = ref.astype(np.float32)
+    rows = np.r_[0:3, 8:n]
+    check(pos[rows] - neg[rows], H[rows], Ws, f)
+    for r in (3, 4):
+        assert np.all(np.isinf(pos[r]) == (ref32[r] > 0)) and np.all(np.isinf(neg[r]) == (ref32[r] < 0))
+    # a NaN sum: what max(NaN, 0) leaves is never an infinity or a finite product
+    assert not np.any(np.isinf(pos[5]) | (pos[5] > 0)) and not np.any(np.isinf(neg[5]) | (neg[5] > 0))
+    assert np.allclose(pos[6, :20], 3.4e38 * 0.25, rtol=1e-6)
+    assert np.isinf(pos[7, 5]) and neg[7, 5] == 0.0
+    for r in (8, 9):
+        mag = np.abs(H[r]).astype(np.float64) @ np.abs(Ws).astype(np.float64)
+        assert np.all(np.abs(pos[r].astype(np.float64) - neg[r] - ref[r]) <= 1e-6 * mag + 1e-43)
+    check(dH, dY, Ws.T, h)
+    # the input gradient, without a ReLU behind it
+    dY[0, 1], dY[1, 2] = np.inf, np.nan
+    dY[2] = np.float32(1e-30)
+    Ws2 = np.abs(Ws)
+    _, _, _, dH = run(np.ones((n, f), np.float32), Ws2, dY)
+    assert np.all(np.isposinf(dH[0])) and np.all(np.isnan(dH[1]))
+    ref = dY[2].astype(np.float64) @ Ws2.T.astype(np.float64)
+    assert np.allclose(dH[2], ref, rtol=2e-6, atol=0)
