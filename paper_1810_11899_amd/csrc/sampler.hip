@@ -397,14 +397,54 @@ __global__ __launch_bounds__(kTB) void rank_kernel(int32_t n, int32_t W, const u
 // wavefronts take the next row from an LDS counter (hub rows of G are
 // hundreds of times longer than the median one).  TABLE_LDS: the list's
 // bitmap (and prefix) copied into LDS first; otherwise read where they are.
+// The neighbour lists (4 bytes a neighbour, from the Infinity Cache or HBM)
+// are what these passes read, and with one 256-byte piece in flight per
+// wavefront their latency bounded them (count 2.14 ms, fill 6.58 ms for 256
+// lists of the Reddit-shaped graph, 1.1 x 10^9 neighbours).  So a wavefront
+// loads kRowChunks pieces at once (2 / 4 / 8 pieces: count 1.39 / 1.24 / 1.15
+// ms), and the rows' bounds are read by the whole block up front instead of as
+// two dependent loads a row.
 constexpr int kRowThreads = 1024;
 constexpr int kRowsPerBlock = 256;
+constexpr int kRowChunks = 8;
 constexpr size_t kInduceMaxLds = 128 * 1024;
 
 __device__ __forceinline__ int32_t next_row(int32_t *ctr, int lane) {
     int32_t r = 0;
     if (lane == 0) r = atomicAdd(ctr, 1);
     return __shfl(r, 0);
+}
+
+// the bounds in G of rows r0 .. r1 - 1 of a list (whole block; r1 - r0 <= kRowsPerBlock)
+__device__ __forceinline__ void load_row_bounds(int2 *rb, const int32_t *indptr, const int32_t *vs, int32_t r0,
+                                                int32_t r1) {
+    for (int32_t r = r0 + (int32_t)threadIdx.x; r < r1; r += kRowThreads) {
+        const int32_t u = vs[r];
+        rb[r - r0] = make_int2(indptr[u], indptr[u + 1]);
+    }
+}
+
+// Calls f(w) for the row's neighbours, 64 at a time in order (lane l of a
+// piece has its l-th neighbour; w = -1 past the row's end), with up to
+// kRowChunks pieces loaded ahead of their use.  Loads past the end are clamped
+// to the row's last neighbour.
+template <class F>
+__device__ __forceinline__ void for_row(const int32_t *__restrict__ indices, int2 b, int lane, F f) {
+    int32_t p0 = b.x;
+    for (; b.y - p0 > 64; p0 += 64 * kRowChunks) {
+        int32_t w[kRowChunks];
+#pragma unroll
+        for (int c = 0; c < kRowChunks; ++c) w[c] = indices[min(p0 + 64 * c + lane, b.y - 1)];
+#pragma unroll
+        for (int c = 0; c < kRowChunks; ++c) {
+            const int32_t p = p0 + 64 * c;
+            if (p < b.y) f(p + lane < b.y ? w[c] : -1);
+        }
+    }
+    if (p0 < b.y) {
+        const int32_t w = indices[min(p0 + lane, b.y - 1)];
+        f(p0 + lane < b.y ? w : -1);
+    }
 }
 
 // row length of every local row: neighbours of vsub[s][i] that are in the list
@@ -416,7 +456,8 @@ __global__ __launch_bounds__(kRowThreads) void row_count_kernel(int32_t nV, int3
                                                                 const int64_t *__restrict__ n_sub,
                                                                 const int32_t *__restrict__ vsub,
                                                                 int32_t *__restrict__ rowlen) {
-    extern __shared__ uint32_t tab[];
+    extern __shared__ __attribute__((aligned(8))) uint32_t tab[];
+    __shared__ int2 rb[kRowsPerBlock];
     __shared__ int32_t ctr;
     const int s = blockIdx.y;
     const int lane = threadIdx.x & 63;
@@ -424,6 +465,7 @@ __global__ __launch_bounds__(kRowThreads) void row_count_kernel(int32_t nV, int3
     const int32_t r1 = (int32_t)min<int64_t>((int64_t)r0 + kRowsPerBlock, min<int64_t>(n_sub[s], n));
     if (r0 >= r1) return;
     const uint32_t *bs = bits + (int64_t)s * W;
+    load_row_bounds(rb, indptr, vsub + (int64_t)s * n, r0, r1);
     if (TABLE_LDS) {
         for (int32_t k = threadIdx.x; k < W; k += kRowThreads) tab[k] = bs[k];
         bs = tab;
@@ -431,13 +473,10 @@ __global__ __launch_bounds__(kRowThreads) void row_count_kernel(int32_t nV, int3
     if (threadIdx.x == 0) ctr = r0;
     __syncthreads();
     for (int32_t i = next_row(&ctr, lane); i < r1; i = next_row(&ctr, lane)) {
-        const int32_t u = vsub[(int64_t)s * n + i];
-        const int32_t p1 = indptr[u + 1];
         int32_t cnt = 0;
-        for (int32_t p = indptr[u] + lane; p < p1; p += 64) {
-            const int32_t w = indices[p];
+        for_row(indices, rb[i - r0], lane, [&](int32_t w) {
             cnt += ((uint32_t)w < (uint32_t)nV) ? (int32_t)((bs[w >> 5] >> (w & 31)) & 1u) : 0;
-        }
+        });
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
         if (lane == 0) rowlen[(int64_t)s * n + i] = cnt;
@@ -445,13 +484,14 @@ __global__ __launch_bounds__(kRowThreads) void row_count_kernel(int32_t nV, int3
 }
 
 // per subgraph: indptr = exclusive scan of the row lengths (one block each);
-// rows past the list's distinct vertices are empty
-__global__ __launch_bounds__(kTB) void row_scan_kernel(int32_t n, const int32_t *__restrict__ rowlen,
+// rows past the list's distinct vertices are empty.  Each length is replaced
+// by the row's mean weight 1 / length (float bits), for the fill pass.
+__global__ __launch_bounds__(kTB) void row_scan_kernel(int32_t n, int32_t *__restrict__ rowlen,
                                                        const int64_t *__restrict__ n_sub,
                                                        int32_t *__restrict__ indptr_sub,
                                                        int64_t *__restrict__ nnz_sub) {
     const int s = blockIdx.x;
-    const int32_t *rl = rowlen + (int64_t)s * n;
+    int32_t *rl = rowlen + (int64_t)s * n;
     int32_t *ip = indptr_sub + (int64_t)s * (n + 1);
     const int64_t ns = n_sub[s];
     int64_t carry = 0;
@@ -461,6 +501,7 @@ __global__ __launch_bounds__(kTB) void row_scan_kernel(int32_t n, const int32_t 
         int64_t total;
         const int64_t ex = block_excl_scan(v, total);
         if (i < n) ip[i] = (int32_t)(carry + ex);
+        if (i < ns) rl[i] = __float_as_int(1.0f / (float)(int32_t)v);
         carry += total;
     }
     if (threadIdx.x == 0) {
@@ -488,7 +529,13 @@ __global__ __launch_bounds__(kTB) void edge_offsets_kernel(int32_t S, const int6
     }
 }
 
-// local column ids and mean weights of every row, in neighbour order
+// local column ids and mean weights of every row, in neighbour order; rinv:
+// the rows' mean weights (row_scan_kernel).  About a third of the neighbours
+// are in the list, so a wavefront collects the ids it finds in an LDS ring and
+// writes them 64 at a time as whole 256-byte pieces of the outputs (a store
+// per 64 neighbours with a third of its lanes active: 4.5 ms, now 3.0 ms
+// for the 351 million edges of 256 lists of the Reddit-shaped graph).
+constexpr int kRing = 128;   // ids per wavefront: fewer than 64 held, up to 64 added
 template <bool TABLE_LDS>
 __global__ __launch_bounds__(kRowThreads) void fill_rows_kernel(int32_t nV, int32_t n, int32_t W,
                                                                 const int32_t *__restrict__ indptr,
@@ -498,12 +545,16 @@ __global__ __launch_bounds__(kRowThreads) void fill_rows_kernel(int32_t nV, int3
                                                                 const int64_t *__restrict__ n_sub,
                                                                 const int32_t *__restrict__ vsub,
                                                                 const int32_t *__restrict__ indptr_sub,
+                                                                const float *__restrict__ rinv,
                                                                 const int64_t *__restrict__ off,
                                                                 const int32_t *__restrict__ status,
                                                                 int32_t *__restrict__ sub_indices,
                                                                 float *__restrict__ sub_vals,
                                                                 float *__restrict__ sub_vals_t) {
-    extern __shared__ uint32_t tab[];
+    extern __shared__ __attribute__((aligned(8))) uint32_t tab[];
+    __shared__ int2 rb[kRowsPerBlock];
+    __shared__ int32_t rp[kRowsPerBlock];
+    __shared__ int32_t rings[kRowThreads / 64 * kRing];
     __shared__ int32_t ctr;
     const int s = blockIdx.y;
     const int lane = threadIdx.x & 63;
@@ -512,42 +563,51 @@ __global__ __launch_bounds__(kRowThreads) void fill_rows_kernel(int32_t nV, int3
     if (*status != 0 || r0 >= r1) return;
     const uint32_t *bs = bits + (int64_t)s * W;
     const int32_t *ps = wpre + (int64_t)s * W;
+    const int32_t *ip = indptr_sub + (int64_t)s * (n + 1);
+    const float *ri = rinv + (int64_t)s * n;
+    load_row_bounds(rb, indptr, vsub + (int64_t)s * n, r0, r1);
+    for (int32_t r = r0 + (int32_t)threadIdx.x; r < r1; r += kRowThreads) rp[r - r0] = ip[r];
     if (TABLE_LDS) {
-        for (int32_t k = threadIdx.x; k < W; k += kRowThreads) {
-            tab[k] = bs[k];
-            tab[W + k] = (uint32_t)ps[k];
-        }
-        bs = tab;
-        ps = (const int32_t *)(tab + W);
+        for (int32_t k = threadIdx.x; k < W; k += kRowThreads) ((uint2 *)tab)[k] = make_uint2(bs[k], (uint32_t)ps[k]);
     }
     if (threadIdx.x == 0) ctr = r0;
     __syncthreads();
-    const int32_t *ip = indptr_sub + (int64_t)s * (n + 1);
+    const int64_t base = off[s];
+    int32_t *const ring = rings + (threadIdx.x >> 6) * kRing;
     for (int32_t i = next_row(&ctr, lane); i < r1; i = next_row(&ctr, lane)) {
-        const int32_t u = vsub[(int64_t)s * n + i];
-        const int32_t len = ip[i + 1] - ip[i];
-        const float val = 1.0f / (float)len;
-        int64_t pos = off[s] + ip[i];
-        const int32_t p1 = indptr[u + 1];
-        for (int32_t p0 = indptr[u]; p0 < p1; p0 += 64) {
-            const int32_t p = p0 + lane;
-            int32_t loc = -1;
-            if (p < p1) {
-                const int32_t w = indices[p];
-                if ((uint32_t)w < (uint32_t)nV) {
-                    const uint32_t word = bs[w >> 5], below = word & ((1u << (w & 31)) - 1u);
-                    if ((word >> (w & 31)) & 1u) loc = ps[w >> 5] + __popc(below);
-                }
-            }
-            const uint64_t mask = __ballot(loc >= 0);
-            if (loc >= 0) {
-                const int64_t q = pos + __popcll(mask & ((1ull << lane) - 1ull));
+        const float val = ri[i];
+        int64_t pos = base + rp[i - r0];   // where the ring's first id goes
+        int32_t head = 0, held = 0;        // the ring holds ids head .. head + held - 1
+        auto flush = [&](int32_t cnt) {
+            if (lane < cnt) {
+                const int32_t loc = ring[(head + lane) & (kRing - 1)];
+                const int64_t q = pos + lane;
                 sub_indices[q] = loc;
                 sub_vals[q] = val;
-                if (sub_vals_t) sub_vals_t[q] = 1.0f / (float)(ip[loc + 1] - ip[loc]);
+                if (sub_vals_t) sub_vals_t[q] = ri[loc];
             }
-            pos += __popcll(mask);
-        }
+            head += cnt;
+            held -= cnt;
+            pos += cnt;
+        };
+        for_row(indices, rb[i - r0], lane, [&](int32_t w) {
+            int32_t loc = -1;
+            if constexpr (TABLE_LDS) {
+                const bool in = (uint32_t)w < (uint32_t)nV;
+                const uint2 e = ((const uint2 *)tab)[in ? w >> 5 : 0];
+                if (in && ((e.x >> (w & 31)) & 1u)) loc = (int32_t)e.y + __popc(e.x & ((1u << (w & 31)) - 1u));
+            } else if ((uint32_t)w < (uint32_t)nV) {
+                const uint32_t word = bs[w >> 5], below = word & ((1u << (w & 31)) - 1u);
+                if ((word >> (w & 31)) & 1u) loc = ps[w >> 5] + __popc(below);
+            }
+            const uint64_t mask = __ballot(loc >= 0);
+            const int32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                           __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+            if (loc >= 0) ring[(head + held + rank) & (kRing - 1)] = loc;
+            held += __popcll(mask);
+            if (held >= 64) flush(64);
+        });
+        while (held > 0) flush(min(held, 64));
     }
 }
 
@@ -612,7 +672,7 @@ struct InduceWs {
     int64_t *tsum;      // [S][tiles]: tile sums, then their exclusive scan
     int64_t *n_sub64;   // [S]
     int64_t *nnz_sub;   // [S]
-    int32_t *rowlen;    // [S][n]
+    int32_t *rowlen;    // [S][n]: row lengths, then the mean weights 1 / length (float bits)
 };
 InduceWs carve_induce(Arena &ar, int32_t nV, int32_t n, int32_t S) {
     InduceWs w;
@@ -783,11 +843,13 @@ int gcn_induce_subgraphs(const gcn_csr *G, int32_t S, int32_t n, const int32_t *
     if (n > 0) {
         if (lds)
             fill_rows_kernel<true><<<rgrid, kRowThreads, fill_lds, s>>>(
-                nV, n, W, G->indptr, G->indices, w.bits, w.wpre, w.n_sub64, vsub, indptr_sub, edge_offsets, status,
+                nV, n, W, G->indptr, G->indices, w.bits, w.wpre, w.n_sub64, vsub, indptr_sub,
+                (const float *)w.rowlen, edge_offsets, status,
                 sub_indices, sub_vals, sub_vals_t);
         else
             fill_rows_kernel<false><<<rgrid, kRowThreads, 0, s>>>(
-                nV, n, W, G->indptr, G->indices, w.bits, w.wpre, w.n_sub64, vsub, indptr_sub, edge_offsets, status,
+                nV, n, W, G->indptr, G->indices, w.bits, w.wpre, w.n_sub64, vsub, indptr_sub,
+                (const float *)w.rowlen, edge_offsets, status,
                 sub_indices, sub_vals, sub_vals_t);
     }
     GCN_LAUNCH_CHECK("induce kernels");

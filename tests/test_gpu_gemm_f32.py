@@ -10,7 +10,7 @@ import torch
 
 from paper_1810_11899_amd import binding as B
 from paper_1810_11899_amd import synth
-from tests.gpu_util import dev, require_gpu
+from gpu_util import dev, require_gpu
 
 pytestmark = pytest.mark.gpu
 

@@ -187,6 +187,28 @@ def test_induce_edge_cases_and_capacity(ws):
     check_induced(g, verts, counts, ib)
 
 
+def test_induce_row_lengths_around_the_loaded_pieces(ws):
+    """Rows of lengths around the 64-neighbour pieces and the 8 loaded at once,
+    with all, half and few of their neighbours in the list."""
+    n = 1400
+    lens = [0, 1, 63, 64, 65, 127, 128, 129, 511, 512, 513, 575, 576, 577, 1024, 1025, 1399, 1400]
+    rows = np.concatenate([np.full(lens[i % len(lens)], i) for i in range(n)])
+    cols = np.concatenate([np.sort((np.arange(lens[i % len(lens)]) * 3 + i) % n)
+                           if lens[i % len(lens)] <= n // 3 else np.arange(lens[i % len(lens)]) for i in range(n)])
+    g = synth.csr_from_pairs(n, rows, cols)
+    rg = np.random.default_rng(3)
+    lists = [rg.permutation(n), rg.permutation(n)[::2], np.arange(0, n, 57), np.arange(40)]
+    verts = np.zeros((len(lists), n), np.int32)
+    counts = np.array([v.size for v in lists], np.int32)
+    for r, v in enumerate(lists):
+        verts[r, :v.size] = v
+    ib = B.InducedBatch(len(lists), n, 4 * g.nnz, "cuda", with_transpose=True)
+    B.gcn_induce_subgraphs(dcsr(g), torch.from_numpy(verts).cuda(), torch.from_numpy(counts).cuda(), ib, ws)
+    torch.cuda.synchronize()
+    assert int(ib.status.item()) == 0
+    check_induced(g, verts, counts, ib)
+
+
 def test_induce_large_graph_table_outside_lds(ws):
     """G of 600,000 vertices: a list's bitmap and prefix (8 bytes per 32
     vertices, 150 KB) exceed what the row kernels hold in LDS, so they read
