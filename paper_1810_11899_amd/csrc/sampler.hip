@@ -22,6 +22,7 @@
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 #include "gcn_sampler.h"
@@ -41,14 +42,15 @@ constexpr int64_t kProbeRoundLimit = 1 << 20;
 struct Words {
     uint64_t w0, w1, w2, w3;
     __device__ __forceinline__ uint64_t get(uint32_t i) const {
-        return i == 0 ? w0 : (i == 1 ? w1 : (i == 2 ? w2 : w3));
+        const uint64_t lo = (i & 1u) ? w1 : w0, hi = (i & 1u) ? w3 : w2;
+        return (i & 2u) ? hi : lo;
     }
 };
 __device__ __forceinline__ Words philox(uint64_t c0, uint64_t kind, uint64_t c2, uint64_t seed, uint64_t sid) {
     const uint64_t M0 = 0xD2E7470EE14C6C93ull, M1 = 0xCA5A826395121157ull;
     const uint64_t W0 = 0x9E3779B97F4A7C15ull, W1 = 0xBB67AE8584CAA73Bull;
     uint64_t x0 = c0, x1 = kind, x2 = c2, x3 = 0, k0 = seed, k1 = sid;
-#pragma unroll
+#pragma unroll 1    // (inlined at a dozen places: unrolled, the sampler outgrows the instruction cache)
     for (int r = 0; r < 10; ++r) {
         const uint64_t lo0 = M0 * x0, hi0 = __umul64hi(M0, x0);
         const uint64_t lo1 = M1 * x2, hi1 = __umul64hi(M1, x2);
@@ -63,6 +65,16 @@ __device__ __forceinline__ Words philox(uint64_t c0, uint64_t kind, uint64_t c2,
 }
 // integer uniform on [0, n): high word of r * n
 __device__ __forceinline__ int64_t below(uint64_t r, int64_t n) { return (int64_t)__umul64hi(r, (uint64_t)n); }
+
+// the same for n < 2^32, in two 32-bit products
+__device__ __forceinline__ uint32_t below32(uint64_t r, uint32_t n) {
+    return (uint32_t)(((r >> 32) * n + (((r & 0xFFFFFFFFull) * n) >> 32)) >> 32);
+}
+// a value all lanes share, in a scalar register
+__device__ __forceinline__ int32_t uniform(int32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ uint64_t uniform64(uint64_t x) {
+    return (uint64_t)(uint32_t)uniform((int32_t)(x >> 32)) << 32 | (uint32_t)uniform((int32_t)x);
+}
 
 __device__ __forceinline__ int32_t weight_of_deg(uint32_t d, int32_t cap) {
     return (cap > 0 && (int32_t)d > cap) ? cap : (int32_t)d;
@@ -96,30 +108,27 @@ struct SampArgs {
 // degree with the live flag (the slot keeps what a pop needs, so popping
 // reads no global memory).
 struct Slots {
+    int2 *bd;        // x: start of the neighbour list, y: degree | kLive
     int32_t *v;
-    int32_t *beg;
-    uint32_t *deg;   // degree | kLive
 };
 
 // Cleanup (Alg. 4): keep the live slots in slot order, renumber them, and
 // rebuild the Dashboard from their weights.  Whole wavefront.
-__device__ void dashboard_cleanup(uint16_t *db, Slots sl, int32_t cap, int32_t &s, int64_t &used) {
+__device__ void dashboard_cleanup(uint16_t *db, Slots sl, int32_t cap, int32_t &s, int32_t &used) {
     const int lane = threadIdx.x;
     int32_t ns = 0;
     for (int32_t base = 0; base < s; base += 64) {
         const int32_t k = base + lane;
         const bool in = k < s;
         const int32_t v = in ? sl.v[k] : 0;
-        const int32_t b = in ? sl.beg[k] : 0;
-        const uint32_t d = in ? sl.deg[k] : 0u;
-        const bool live = in && (d & kLive);
+        const int2 bd = in ? sl.bd[k] : make_int2(0, 0);
+        const bool live = in && ((uint32_t)bd.y & kLive);
         const uint64_t mask = __ballot(live);
         const int rank = __popcll(mask & ((1ull << lane) - 1ull));
         __syncthreads();            // every lane has read its slot before any moves
         if (live) {
             sl.v[ns + rank] = v;
-            sl.beg[ns + rank] = b;
-            sl.deg[ns + rank] = d;
+            sl.bd[ns + rank] = bd;
         }
         ns += __popcll(mask);
         __syncthreads();
@@ -128,23 +137,23 @@ __device__ void dashboard_cleanup(uint16_t *db, Slots sl, int32_t cap, int32_t &
     int64_t off = 0;
     for (int32_t base = 0; base < ns; base += 64) {
         const int32_t k = base + lane;
-        const int32_t w = k < ns ? weight_of_deg(sl.deg[k] & ~kLive, cap) : 0;
+        const int32_t w = k < ns ? weight_of_deg((uint32_t)sl.bd[k].y & ~kLive, cap) : 0;
         const int64_t incl = wave_incl_scan(w);
         const int64_t start = off + incl - w;
         for (int32_t e = 0; e < w; ++e) db[start + e] = (uint16_t)k;
         off += __shfl(incl, 63, 64);
     }
-    used = off;
+    used = uniform((int32_t)off);
     __syncthreads();
 }
 
+template <bool AHEAD>
 __global__ __launch_bounds__(kSampThreads) void frontier_kernel(SampArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     Slots sl;
-    sl.v = (int32_t *)lds;                              // [ia_cap]
-    sl.beg = sl.v + a.ia_cap;                           // [ia_cap]
-    sl.deg = (uint32_t *)(sl.beg + a.ia_cap);           // [ia_cap]
-    uint16_t *db = (uint16_t *)(sl.deg + a.ia_cap);     // Dashboard [db_cap]
+    sl.bd = (int2 *)lds;                                // [ia_cap]
+    sl.v = (int32_t *)(sl.bd + a.ia_cap);               // [ia_cap]
+    uint16_t *db = (uint16_t *)(sl.v + a.ia_cap);       // Dashboard [db_cap]
     const int lane = threadIdx.x;
     const uint64_t sid = (uint64_t)(a.first_sampler + blockIdx.x);
     int32_t *out = a.vertices + (int64_t)blockIdx.x * a.n;
@@ -178,7 +187,7 @@ __global__ __launch_bounds__(kSampThreads) void frontier_kernel(SampArgs a) {
         count = got;
     }
 
-    int64_t used = 0, live_weight = 0;
+    int32_t used = 0, live_weight = 0;   // at most db_cap entries
     int32_t s = 0;
     if (status == GCN_SAMPLE_OK) {
         // ---- Dashboard from the roots (Alg. 3, initialisation)
@@ -194,14 +203,14 @@ __global__ __launch_bounds__(kSampThreads) void frontier_kernel(SampArgs a) {
             const int32_t w = weight_of_deg(d, a.cap);
             const int64_t incl = wave_incl_scan(w);
             const int64_t total = __shfl(incl, 63, 64);
-            if (used + total > a.db_cap) { status = GCN_SAMPLE_OVERFLOW; break; }
+            const bool over = __builtin_amdgcn_readfirstlane((int)(used + total > a.db_cap)) != 0;
+            if (over) { status = GCN_SAMPLE_OVERFLOW; break; }
             const int64_t start = used + incl - w;
             if (k < a.m) {
-                sl.beg[k] = b;
-                sl.deg[k] = d | kLive;
+                sl.bd[k] = make_int2(b, (int32_t)(d | kLive));
                 for (int32_t e = 0; e < w; ++e) db[start + e] = (uint16_t)k;
             }
-            used += total;
+            used += uniform((int32_t)total);
         }
         live_weight = used;
         s = a.m;
@@ -209,73 +218,200 @@ __global__ __launch_bounds__(kSampThreads) void frontier_kernel(SampArgs a) {
     }
 
     // ---- main loop: pop a frontier vertex, step to a neighbour, add it.
-    // Random blocks are drawn ahead, while the step's global loads are in
-    // flight: probe block r/4 of this lane, neighbour block t/4.
-    uint64_t round = 0;
-    int64_t pblk = -1, nblk = -1;
+    //
+    // A step is two dependent loads (the neighbour, then its row bounds), and
+    // the next step's pop needs the second one's result: how many entries the
+    // new vertex adds.  With a cap that number is nearly always the cap (the
+    // walk prefers vertices of high degree), so with AHEAD two more steps are
+    // popped on that guess: iteration i issues the neighbour load of step
+    // i + 2 and the row-bound loads of step i + 1, and appends step i, whose
+    // loads have had an iteration each.  An append of fewer entries takes the
+    // pops behind it back (their vertices are live again) and they are drawn
+    // anew from the same random words, so the run is the sequential one.
+    // The loads of the steady path are issued in every iteration, needed or
+    // not, and the paths that fill it wait for theirs: each use then waits for
+    // its own load and not for the later ones.
+    // A step is also some hundred instructions of one wavefront, hence the
+    // scalar branches, the shared Philox calls and the branch-free writes.
+    // 256 runs, m = 1000, n = 8000, cap 30: 9.24 ms one step at a time (1.32 us
+    // each), now 6.95 ms.
+    struct Step {
+        int32_t k, v, b, e;   // popped slot; its neighbour; the neighbour's row bounds (loads in flight)
+        uint32_t deg;         // degree of the popped vertex
+        uint64_t round;       // probing rounds used up to and with this pop
+    };
+    Step q[3] = {};
+    uint64_t round = 0;       // ... up to the last append
+    int32_t popped = 0;       // steps popped from step i on: q[phase], q[phase + 1], ...
+    uint64_t pblk = ~0ull - 8;
+    int32_t nblk = -64, prov = 0;   // prov: slots below it have cap entries written ahead
     Words pw{0, 0, 0, 0}, nw{0, 0, 0, 0};
-    for (int32_t i = a.m; status == GCN_SAMPLE_OK && i < a.n; ++i) {
-        if (live_weight == 0) { status = GCN_SAMPLE_EXHAUSTED; break; }
-        const uint64_t t = (uint64_t)(i - a.m);
-        if ((int64_t)(t >> 2) != nblk) {
-            nw = philox(t >> 2, kKindNeigh, 0, a.seed, sid);
-            nblk = (int64_t)(t >> 2);
-        }
-        const uint64_t rn = nw.get((uint32_t)(t & 3));
-        int32_t k = -1;
-        for (int64_t rr = 0;; ++rr) {
-            if (rr >= kProbeRoundLimit) { status = GCN_SAMPLE_PROBE_LIMIT; break; }
-            if ((int64_t)(round >> 2) != pblk) {
-                pw = philox(round >> 2, kKindProbe, (uint64_t)lane, a.seed, sid);
-                pblk = (int64_t)(round >> 2);
+    int32_t i = a.m, flushed = a.m, held = 0;   // vertices flushed .. i - 1 wait in `held`, one per lane
+    // ordering of this wavefront's LDS accesses (they execute in order)
+    auto lds_order = []() __attribute__((always_inline)) { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
+    // Probing rounds until one hits: the lowest of the 64 processors on a live
+    // entry wins.  It is nearly always among the first 16, so only their words
+    // are drawn, for 16 rounds at once (lane l: processor l % 16, Philox block
+    // pblk + l / 16); a round they all miss is drawn for the other 48.
+    auto probe = [&](int32_t in_use, uint64_t &rnd, int32_t limit) __attribute__((always_inline)) -> int32_t {
+        for (int32_t rr = 0; rr < limit; ++rr) {
+            const uint64_t blk = rnd >> 2;
+            if (blk - pblk >= 4u) {
+                pw = philox(blk + (lane >> 4), kKindProbe, (uint64_t)(lane & 15), a.seed, sid);
+                pblk = blk;
             }
-            const int64_t idx = below(pw.get((uint32_t)(round & 3)), used);
-            const int32_t slot = db[idx];
-            const uint64_t mask = __ballot((sl.deg[slot] & kLive) != 0u);
-            ++round;
-            if (mask) {
-                k = __shfl(slot, __ffsll((unsigned long long)mask) - 1, 64);
-                break;
+            const int g = 16 * (int)(blk - pblk);
+            const uint32_t wi = (uint32_t)rnd & 3u;
+            ++rnd;
+            int32_t slot = db[below32(pw.get(wi), (uint32_t)in_use)];
+            uint64_t mask = __ballot(((uint32_t)sl.bd[slot].y & kLive) != 0u) & (0xFFFFull << g);
+            if (__builtin_expect(mask == 0, 0)) {
+                const Words x = philox(blk, kKindProbe, (uint64_t)lane, a.seed, sid);
+                slot = db[below32(x.get(wi), (uint32_t)in_use)];
+                mask = __ballot(((uint32_t)sl.bd[slot].y & kLive) != 0u);
             }
+            if (mask) return __builtin_amdgcn_readlane(slot, __ffsll((unsigned long long)mask) - 1);
         }
-        if (status != GCN_SAMPLE_OK) break;
-        const int32_t beg = sl.beg[k];
-        const uint32_t deg = sl.deg[k] & ~kLive;    // >= 1: its weight was > 0
-        __syncthreads();
-        if (lane == 0) sl.deg[k] = deg;             // no longer in the frontier
-        live_weight -= weight_of_deg(deg, a.cap);
-
-        const int32_t v_new = a.indices[beg + below(rn, (int64_t)deg)];
-        // draw ahead while the load is in flight
-        if ((int64_t)((t + 1) >> 2) != nblk) {
-            nw = philox((t + 1) >> 2, kKindNeigh, 0, a.seed, sid);
-            nblk = (int64_t)((t + 1) >> 2);
+        return -1;
+    };
+    // vector loads of one word (all lanes the same): the scalar unit's loads
+    // would share the LDS reads' wait counter
+    auto load1 = [&](const int32_t *base, int64_t at) __attribute__((always_inline)) {
+        uint32_t lo = (uint32_t)at;
+        asm volatile("" : "+v"(lo));
+        return base[lo];
+    };
+    // the loads of x are done
+    auto landed = [&](Step &x) __attribute__((always_inline)) { asm volatile("" : "+v"(x.v), "+v"(x.b), "+v"(x.e)); };
+    // slot k leaves the frontier as step t; returns where its neighbour is.
+    // Neighbour words: lane l holds the Philox block nblk + l (four steps each).
+    auto take = [&](Step &x, int32_t k, int32_t t) __attribute__((always_inline)) -> int64_t {
+        const int2 bd = sl.bd[k];
+        const int32_t beg = uniform(bd.x);
+        x.k = k;
+        x.deg = (uint32_t)uniform(bd.y) & ~kLive;   // >= 1: its weight was > 0
+        lds_order();
+        sl.bd[k].y = (int32_t)x.deg;                // no longer in the frontier
+        lds_order();
+        const int32_t blk = t >> 2;
+        if ((uint32_t)(blk - nblk) >= 64u) {
+            nw = philox((uint64_t)(blk + lane), kKindNeigh, 0, a.seed, sid);
+            nblk = blk;
         }
-        if ((int64_t)(round >> 2) != pblk) {
-            pw = philox(round >> 2, kKindProbe, (uint64_t)lane, a.seed, sid);
-            pblk = (int64_t)(round >> 2);
+        const uint64_t word = nw.get((uint32_t)(t & 3));
+        const int src = (int)(blk - nblk);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)word, src);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(word >> 32), src);
+        return (int64_t)beg + below32(((uint64_t)hi << 32) | lo, x.deg);
+    };
+    auto bounds = [&](Step &x) __attribute__((always_inline)) {
+        const int32_t u = (uint32_t)x.v < (uint32_t)a.nV ? x.v : 0;
+        x.b = load1(a.indptr, u);
+        x.e = load1(a.indptr + 1, u);
+    };
+    // pop step i + j ahead (popped == j), as if steps i .. i + j - 1 append cap
+    // entries each; returns where its neighbour is, or 0 without a pop
+    auto ahead = [&](Step &x, const Step &prev, int32_t j) __attribute__((always_inline)) -> int64_t {
+        if ((int)(popped != j) | (int)(i + j >= a.n) | (int)(used + j * a.cap > a.db_cap) | (int)(s + j > a.ia_cap))
+            return 0;
+        const int32_t ps = s + j - 1;               // the slot step i + j - 1 will take
+        const int32_t pb = used + (j - 1) * a.cap;
+        // (lanes past the end, and all lanes of a slot write, store the same
+        // value again: no branch over the exec mask)
+        for (int32_t e0 = 0; e0 < a.cap; e0 += 64) db[pb + min(e0 + lane, a.cap - 1)] = (uint16_t)ps;
+        sl.bd[ps].y = (int32_t)kLive;
+        prov = ps + 1;
+        lds_order();
+        uint64_t rnd = prev.round;
+        const int32_t k = probe(used + j * a.cap, rnd, 8);
+        if (k < 0 || k >= s) return 0;              // none, or a vertex that is not known yet
+        x.round = rnd;
+        popped = j + 1;
+        return take(x, k, i - a.m + j);
+    };
+    auto step = [&](auto phase) __attribute__((always_inline)) -> bool {
+        constexpr int P = decltype(phase)::value;
+        Step &c = q[P], &n1 = q[(P + 1) % 3], &n2 = q[(P + 2) % 3];
+        // (the same in every lane; said here so that the step's branches and
+        // arithmetic are scalar)
+        s = uniform(s);
+        used = uniform(used);
+        live_weight = uniform(live_weight);
+        popped = uniform(popped);
+        prov = uniform(prov);
+        i = uniform(i);
+        flushed = uniform(flushed);
+        round = uniform64(round);
+        c.round = uniform64(c.round);
+        n1.round = uniform64(n1.round);
+        c.k = uniform(c.k);
+        n1.k = uniform(n1.k);
+        c.deg = (uint32_t)uniform((int32_t)c.deg);
+        pblk = uniform64(pblk);
+        nblk = uniform(nblk);
+        if (live_weight == 0) { status = GCN_SAMPLE_EXHAUSTED; return false; }
+        if (popped < (AHEAD ? 2 : 1)) {
+            if (popped == 0) {
+                c.round = round;
+                const int32_t k = probe(used, c.round, (int32_t)kProbeRoundLimit);
+                if (k < 0) { status = GCN_SAMPLE_PROBE_LIMIT; return false; }
+                c.v = load1(a.indices, take(c, k, i - a.m));
+                popped = 1;
+                bounds(c);
+            }
+            if (AHEAD) n1.v = load1(a.indices, ahead(n1, c, 1));
+            landed(c);
+            if (AHEAD) landed(n1);
         }
-        if ((uint32_t)v_new >= (uint32_t)a.nV) { status = GCN_SAMPLE_BAD_GRAPH; break; }
-        const int32_t b2 = a.indptr[v_new];
-        const uint32_t d2 = (uint32_t)(a.indptr[v_new + 1] - b2);
+        if (AHEAD) {
+            n2.v = load1(a.indices, ahead(n2, n1, 2));
+            bounds(n1);
+        }
+        // append step i
+        const int32_t v = uniform(c.v), b = uniform(c.b);
+        if ((uint32_t)v >= (uint32_t)a.nV) { status = GCN_SAMPLE_BAD_GRAPH; return false; }
+        const uint32_t d2 = (uint32_t)(uniform(c.e) - b);
         const int32_t w = weight_of_deg(d2, a.cap);
-
-        __syncthreads();
-        if (used + w > a.db_cap || s == a.ia_cap) dashboard_cleanup(db, sl, a.cap, s, used);
-        if (used + w > a.db_cap) { status = GCN_SAMPLE_OVERFLOW; break; }
-        for (int32_t e = lane; e < w; e += 64) db[used + e] = (uint16_t)s;
-        if (lane == 0) {
-            sl.v[s] = v_new;
-            sl.beg[s] = b2;
-            sl.deg[s] = d2 | kLive;
-            out[i] = v_new;
+        live_weight -= weight_of_deg(c.deg, a.cap);
+        round = c.round;
+        // (with pops ahead there is room for cap >= w entries and a slot)
+        if ((int64_t)used + w > a.db_cap || s == a.ia_cap) {
+            __syncthreads();
+            dashboard_cleanup(db, sl, a.cap, s, used);
+            prov = 0;
         }
+        if ((int64_t)used + w > a.db_cap) { status = GCN_SAMPLE_OVERFLOW; return false; }
+        if (!AHEAD || s >= prov)                    // not written ahead
+            for (int32_t e0 = 0; e0 < w; e0 += 64)
+                if (e0 + lane < w) db[used + e0 + lane] = (uint16_t)s;
+        sl.v[s] = v;
+        sl.bd[s] = make_int2(b, (int32_t)(d2 | kLive));
+        if (lane == (i & 63)) held = v;
         used += w;
         live_weight += w;
         ++s;
-        count = i + 1;
-        __syncthreads();
-    }
+        count = ++i;
+        --popped;
+        if (AHEAD && w != a.cap && popped > 0) {    // the guess was wrong
+            if (lane == 0) {
+                sl.bd[n1.k].y |= (int32_t)kLive;
+                if (popped > 1) sl.bd[n2.k].y |= (int32_t)kLive;
+            }
+            popped = 0;
+            prov = s;
+        }
+        lds_order();
+        if (i - flushed == 64) {
+            out[flushed + ((lane - flushed) & 63)] = held;
+            flushed = i;
+        }
+        return i < a.n;
+    };
+    if (status == GCN_SAMPLE_OK && i < a.n)
+        while (step(std::integral_constant<int, 0>{}) && step(std::integral_constant<int, 1>{}) &&
+               step(std::integral_constant<int, 2>{})) {
+        }
+    if (flushed + ((lane - flushed) & 63) < i) out[flushed + ((lane - flushed) & 63)] = held;
     if (lane == 0) {
         a.counts[blockIdx.x] = count;
         a.status[blockIdx.x] = status;
@@ -650,13 +786,16 @@ size_t sampler_lds_bytes(int32_t db_cap, int32_t ia_cap) {
 }
 
 int frontier_sample(const SampArgs &a, int32_t S, size_t lds, hipStream_t s) {
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipFuncSetAttribute((const void *)frontier_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+    static std::once_flag attr;
+    std::call_once(attr, [] {
+        hipFuncSetAttribute((const void *)frontier_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             kSamplerMaxLds);
-        attr_set = true;
-    }
-    frontier_kernel<<<S, kSampThreads, lds, s>>>(a);
+        hipFuncSetAttribute((const void *)frontier_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            kSamplerMaxLds);
+    });
+    // without a cap a vertex's entries are its degree, which cannot be guessed
+    if (a.cap > 0) frontier_kernel<true><<<S, kSampThreads, lds, s>>>(a);
+    else frontier_kernel<false><<<S, kSampThreads, lds, s>>>(a);
     GCN_LAUNCH_CHECK("frontier_kernel");
     return GCN_OK;
 }

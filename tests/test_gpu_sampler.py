@@ -259,3 +259,15 @@ def test_gather_labels_int32():
     out = torch.empty(5, dtype=torch.int32, device="cuda")
     B.gcn_gather_rows(torch.from_numpy(labels).cuda(), torch.from_numpy(rows).cuda(), 5, out)
     assert np.array_equal(out.cpu().numpy(), labels[rows])
+
+
+@pytest.mark.parametrize("cap, m, n", [(1, 7, 400), (5, 64, 1500), (63, 100, 1200), (64, 100, 1200), (65, 100, 1200),
+                                       (130, 60, 900)])
+def test_frontier_pops_ahead_match_oracle(cap, m, n):
+    """Caps around a wavefront's width on a graph whose degrees fall on both
+    sides of them, so that pops made ahead are kept, taken back and blocked by
+    vertices not yet known, with few and many cleanups between them."""
+    g = synth.custom(1500, "rmat", 24, [(4, 4)], seed=cap).graph
+    wmax = int(np.minimum(g.degrees(), cap).max())
+    run_and_compare(g, params_for(g, m, n, cap=cap, seed=3), 4)
+    run_and_compare(g, params_for(g, m, n, cap=cap, seed=4, db=m * wmax + cap, ia=m + 3), 4, first=2)
