@@ -161,17 +161,29 @@ struct LayerPlan {
 // k-major operand tiles are read transposed from LDS.  Then no transposed
 // copy of those operands is made.  Otherwise (shapes the large-tile kernel
 // does not take) the products run NT on transposed copies.
-bool bf16_dw_rowmajor(int32_t n, int32_t f_in, int32_t h) {
+//
+// A layer that converts its input itself keeps the rows (and AGG's) with zero
+// columns up to a multiple of 8; `packed`: the input rows come from the layer
+// below with leading dimension f_in.
+int32_t pad8(int32_t f) { return (f + 7) & ~7; }
+bool bf16_dw_rowmajor(int32_t n, int32_t f_in, int32_t h, bool packed) {
     if (n <= 0) return false;
     const void *p = (const void *)(uintptr_t)256;   // stands for 256-byte aligned buffers
     GemmProblem g[2] = {};
     for (int i = 0; i < 2; ++i) {
         g[i].M = f_in;
         g[i].N = h;
-        g[i].seg[0] = GemmSeg{p, f_in, p, 2 * (int64_t)h, n};
+        g[i].seg[0] = GemmSeg{p, packed ? f_in : pad8(f_in), p, 2 * (int64_t)h, n};
     }
     return gemm_bf16_big_ok(L_TN, 2, g) && h % 8 == 0;
 }
+
+// leading dimension of a bfloat16 layer's input rows H16 and AGG16
+int32_t bf16_ld(int32_t n, int32_t f_in, int32_t h, bool packed) {
+    return !packed && bf16_dw_rowmajor(n, f_in, h, false) ? pad8(f_in) : f_in;
+}
+// one of the four copies in a bfloat16 layer's saved buffer
+size_t saved_one(int32_t n, int32_t f_in) { return align256((size_t)n * pad8(f_in) * 2); }
 
 int32_t pad_classes(int32_t C);
 
@@ -229,7 +241,7 @@ LayerPlan plan_layer(int32_t n, int32_t nnz, int32_t f_in, int32_t h, int order,
     p.need_G = bwd_uses_G(order, dH, f_in, h);
     p.bf16 = prec == GCN_BF16;
     const size_t E = p.bf16 ? 2 : 4;  // bytes per stored intermediate element
-    const size_t W16 = p.bf16 ? 2 * align256((size_t)f_in * h * 2) : 0;
+    const size_t W16 = p.bf16 ? 2 * align256((size_t)pad8(f_in) * h * 2) : 0;
     // bfloat16 products run with both operands contiguous along K: the
     // backward also keeps P^T (and dZ_n^T for aggregate-first with G)
     p.bwd_PT = p.bf16 ? align256((size_t)n * 2 * h * 2) : 0;
@@ -238,7 +250,7 @@ LayerPlan plan_layer(int32_t n, int32_t nnz, int32_t f_in, int32_t h, int order,
         p.fwd_T = align256((size_t)n * h * E);
         p.fwd_spmm = spmm_workspace_bytes(n, nnz, h);
     } else {
-        p.fwd_spmm = spmm_workspace_bytes(n, nnz, f_in);
+        p.fwd_spmm = spmm_workspace_bytes(n, nnz, p.bf16 ? pad8(f_in) : f_in);
     }
     p.fwd_W16 = W16;
     // split-K partials of the forward products, when there are too few row
@@ -291,11 +303,11 @@ LayerPlan plan_layer(int32_t n, int32_t nnz, int32_t f_in, int32_t h, int order,
 }
 
 // float32: AGG (aggregate-first only).  bfloat16: H16, H16^T, then AGG16 and
-// AGG16^T (aggregate-first), each n x f_in.
+// AGG16^T (aggregate-first), each n x f_in (rows of up to pad8(f_in)).
 size_t saved_bytes(int32_t n, int32_t f_in, int32_t h, int order, int prec) {
     (void)h;
     if (prec == GCN_BF16) {
-        const size_t one = align256((size_t)n * f_in * 2);
+        const size_t one = saved_one(n, f_in);
         return order == GCN_AGGREGATE_FIRST ? 4 * one : 2 * one;
     }
     if (order == GCN_AGGREGATE_FIRST) return align256((size_t)n * f_in * sizeof(float));
@@ -487,31 +499,36 @@ static int layer_fwd(bool launch, const gcn_csr *A, const float *H, int32_t f_in
     if (bf) {
         // bfloat16 operands, every product in NT form (both operands contiguous
         // along K); saved = H16 | H16^T | AGG16 | AGG16^T
-        const size_t one = align256((size_t)n * f_in * 2);
+        const size_t one = saved_one(n, f_in);
         uint16_t *H16 = (uint16_t *)saved;
         uint16_t *H16T = (uint16_t *)((char *)saved + one);
         uint16_t *AGG16 = af ? (uint16_t *)((char *)saved + 2 * one) : nullptr;
         uint16_t *AGG16T = af ? (uint16_t *)((char *)saved + 3 * one) : nullptr;
-        uint16_t *WsT = ar.take<uint16_t>((size_t)f_in * h);
-        uint16_t *WnT = ar.take<uint16_t>((size_t)f_in * h);
+        uint16_t *WsT = ar.take<uint16_t>((size_t)pad8(f_in) * h);
+        uint16_t *WnT = ar.take<uint16_t>((size_t)pad8(f_in) * h);
         // H16 (and H16T for the transposed weight-gradient products) in one
         // pass over H, unless the layer below wrote them
-        const bool tnw = bf16_dw_rowmajor(n, f_in, h);
+        const bool tnw = bf16_dw_rowmajor(n, f_in, h, lk.in_ready);
+        const int32_t fp = bf16_ld(n, f_in, h, lk.in_ready);   // the rows of H16, AGG16, W^T
         if (!lk.in_ready) {
-            rc = tnw ? cvt_bf16(n, f_in, H, ldh, H16, f_in, s) : transpose_bf16_copy(n, f_in, H, 0, ldh, H16T, n, H16, f_in, s);
+            rc = tnw ? cvt_bf16_pad(n, f_in, H, ldh, H16, fp, fp, s)
+                     : transpose_bf16_copy(n, f_in, H, 0, ldh, H16T, n, H16, f_in, s);
             if (rc) return rc;
         }
         if (lk.WsT) {
             WsT = const_cast<uint16_t *>(lk.WsT);
             WnT = const_cast<uint16_t *>(lk.WnT);
         } else {
-            if ((rc = transpose_bf16(f_in, h, W_self, 0, h, WsT, f_in, s))) return rc;
-            if ((rc = transpose_bf16(f_in, h, W_neigh, 0, h, WnT, f_in, s))) return rc;
+            Bf16PrepBatch wb;
+            wb.add(W_self, h, f_in, h, WsT, fp, fp, true);
+            wb.add(W_neigh, h, f_in, h, WnT, fp, fp, true);
+            if ((rc = prep_bf16(wb, s))) return rc;
         }
         GemmProblem g[2] = {};
         g[0].M = g[1].M = n;
         g[0].N = g[1].N = h;
-        g[0].seg[0] = GemmSeg{H16, f_in, WsT, f_in, f_in};
+        g[0].seg[0] = GemmSeg{H16, fp, WsT, fp, fp};
+        g[0].k_pad = g[1].k_pad = fp - f_in;
         g[0].C = Y;
         g[0].ldc = ldy;
         g[0].bias = bias;
@@ -530,11 +547,11 @@ static int layer_fwd(bool launch, const gcn_csr *A, const float *H, int32_t f_in
         link_out(g[0], 0);
         if (af) {
             void *sw = ar.take<char>(pl.fwd_spmm);
-            rc = spmm_bf16(n, A->nnz, A->indptr, idx_of(A), A->vals, H16, f_in, f_in, AGG16, f_in,
+            rc = spmm_bf16(n, A->nnz, A->indptr, idx_of(A), A->vals, H16, fp, fp, AGG16, fp,
                            EPI_STORE_BF16, nullptr, sw, pl.fwd_spmm, s, bA);
             if (rc) return rc;
             if (!tnw && (rc = transpose_bf16(n, f_in, AGG16, 1, f_in, AGG16T, n, s))) return rc;
-            g[1].seg[0] = GemmSeg{AGG16, f_in, WnT, f_in, f_in};
+            g[1].seg[0] = GemmSeg{AGG16, fp, WnT, fp, fp};
             g[1].C = Y ? Y + h : nullptr;   // no float32 copy when Y is NULL
             g[1].ldc = ldy;
             g[1].bias = bias + h;
@@ -546,7 +563,7 @@ static int layer_fwd(bool launch, const gcn_csr *A, const float *H, int32_t f_in
         }
         uint16_t *T16 = (uint16_t *)ar.take<char>(pl.fwd_T);
         void *sw = ar.take<char>(pl.fwd_spmm);
-        g[1].seg[0] = GemmSeg{H16, f_in, WnT, f_in, f_in};
+        g[1].seg[0] = GemmSeg{H16, fp, WnT, fp, fp};
         g[1].C16 = T16;
         g[1].ldc = h;
         void *gw = pl.fwd_gemm ? ar.take<char>(pl.fwd_gemm) : nullptr;
@@ -599,7 +616,8 @@ static int layer_bwd(bool launch, const gcn_csr *A, const gcn_csr *AT, const flo
                      void *ws, size_t ws_bytes, void *stream, bool dz_ready = false,
                      float *below_dbias = nullptr, const int32_t *bAT = nullptr, bool dzT_ready = false,
                      int32_t below_tcols = 0, const uint16_t *Ws16_ready = nullptr,
-                     const uint16_t *Wn16_ready = nullptr) {
+                     const uint16_t *Wn16_ready = nullptr, bool packed = false) {
+    // packed (bfloat16): the saved input rows came from the layer below
     // bAT: A^T's merge-path row ranges (spmm_bounds), or NULL
     // dzT_ready (bfloat16, with dz_ready): the producer of dY also wrote
     // dZ^T (2h x n, leading dim n) behind the packed dZ rows in the same
@@ -690,18 +708,19 @@ static int layer_bwd(bool launch, const gcn_csr *A, const gcn_csr *AT, const flo
     // a7: weight gradients, K = n, split-K
     GemmProblem g[2] = {dw_problem(f_in, h, n), dw_problem(f_in, h, n)};
     int layout = L_TN;
-    if (bf && bf16_dw_rowmajor(n, f_in, h)) {
+    if (bf && bf16_dw_rowmajor(n, f_in, h, packed)) {
         // TN form on the row-major operands: dW_self = H^T dZ_s, dW_neigh =
         // AGG^T dZ_n (aggregate-first) or H^T G (transform-first)
-        const size_t one = align256((size_t)n * f_in * 2);
+        const size_t one = saved_one(n, f_in);
+        const int32_t fp = bf16_ld(n, f_in, h, packed);
         const uint16_t *H16 = (const uint16_t *)saved;
         layout = L_TN;
-        g[0].seg[0] = GemmSeg{H16, f_in, Zs, ldZs, n};
-        if (!af) g[1].seg[0] = GemmSeg{H16, f_in, Gp, ldG, n};
-        else g[1].seg[0] = GemmSeg{(const char *)saved + 2 * one, f_in, Zn, ldZn, n};
+        g[0].seg[0] = GemmSeg{H16, fp, Zs, ldZs, n};
+        if (!af) g[1].seg[0] = GemmSeg{H16, fp, Gp, ldG, n};
+        else g[1].seg[0] = GemmSeg{(const char *)saved + 2 * one, fp, Zn, ldZn, n};
     } else if (bf) {
         // NT form: dW = (H^T) (P^T)^T with H^T (f_in x n) and P^T (2h x n) contiguous along n
-        const size_t one = align256((size_t)n * f_in * 2);
+        const size_t one = saved_one(n, f_in);
         const uint16_t *H16T = (const uint16_t *)((const char *)saved + one);
         const uint16_t *AGG16T = af ? (const uint16_t *)((const char *)saved + 3 * one) : nullptr;
         uint16_t *PT = (uint16_t *)ar.take<char>(pl.bwd_PT);
@@ -1079,10 +1098,11 @@ static size_t model_w16_bytes(int32_t n, int32_t L, const gcn_layer_args *layers
     for (int32_t l = 0; l < L; ++l) {
         const gcn_layer_args &a = layers[l];
         const size_t one = (size_t)a.f_in * a.h * 2;
-        uint16_t *st = carve(one), *nt = carve(one);
+        const int32_t fp = bf16_ld(n, a.f_in, a.h, l > 0);
+        uint16_t *st = carve((size_t)fp * a.h * 2), *nt = carve((size_t)fp * a.h * 2);
         if (batch) {
-            batch->add(a.W_self, a.h, a.f_in, a.h, st, a.f_in, 0, true);
-            batch->add(a.W_neigh, a.h, a.f_in, a.h, nt, a.f_in, 0, true);
+            batch->add(a.W_self, a.h, a.f_in, a.h, st, fp, fp, true);
+            batch->add(a.W_neigh, a.h, a.f_in, a.h, nt, fp, fp, true);
             out->WsT[l] = st;
             out->WnT[l] = nt;
         }
@@ -1101,7 +1121,7 @@ static size_t model_w16_bytes(int32_t n, int32_t L, const gcn_layer_args *layers
         uint16_t *wp = carve((size_t)f * Cp * 2), *wpt = carve((size_t)f * C * 2);
         if (batch) {
             batch->add(head->W_pred, C, f, C, wp, Cp, Cp, false);
-            batch->add(head->W_pred, C, f, C, wpt, f, 0, true);
+            batch->add(head->W_pred, C, f, C, wpt, f, f, true);
             out->Wp16 = wp;
             out->Wp16T = wpt;
         }
@@ -1182,8 +1202,8 @@ int model_step(bool launch, const gcn_csr *A, const gcn_csr *AT, const float *H0
             if (l + 1 < L) {
                 const gcn_layer_args &nx = layers[l + 1];
                 lk.out16 = (uint16_t *)nx.saved;
-                if (!bf16_dw_rowmajor(n, nx.f_in, nx.h))   // only the transposed products read H16T
-                    lk.out16T = (uint16_t *)((char *)nx.saved + align256((size_t)n * nx.f_in * 2));
+                if (!bf16_dw_rowmajor(n, nx.f_in, nx.h, true))   // only the transposed products read H16T
+                    lk.out16T = (uint16_t *)((char *)nx.saved + saved_one(n, nx.f_in));
             } else if (head) {
                 lk.out16 = HL16;
                 if (!head_dw_rowmajor(n, 2 * a.h, head->C)) lk.out16T = HL16T;   // read by an NT dW_pred only
@@ -1201,7 +1221,7 @@ int model_step(bool launch, const gcn_csr *A, const gcn_csr *AT, const float *H0
     // aggregate-first (dW_self and dW_neigh), the self half for
     // transform-first (dW_neigh takes A^T dZ_n, transposed after the SpMM)
     auto tcols = [&](int32_t l) {
-        if (!bf || bf16_dw_rowmajor(n, layers[l].f_in, layers[l].h)) return 0;
+        if (!bf || bf16_dw_rowmajor(n, layers[l].f_in, layers[l].h, l > 0)) return 0;
         return layers[l].order == GCN_AGGREGATE_FIRST ? 2 * layers[l].h : layers[l].h;
     };
     const float *g = dY;  // PREDICT + LOSS, or the given output gradient
@@ -1230,7 +1250,7 @@ int model_step(bool launch, const gcn_csr *A, const gcn_csr *AT, const float *H0
         if ((rc = layer_bwd(launch, A, AT, Hin, a.f_in, ldin, a.W_self, a.W_neigh, a.h, a.Y, a.ldy, a.saved,
                             a.saved_bytes, g, ldg, a.dH, a.lddh, a.dW_self, a.dW_neigh, a.dbias, a.order, prec, ws,
                             ws_bytes, stream, ready, fuse ? layers[l - 1].dbias : nullptr, bAT,
-                            ready && tcols(l) > 0, fuse ? tcols(l - 1) : 0, w16.Ws16[l], w16.Wn16[l])))
+                            ready && tcols(l) > 0, fuse ? tcols(l - 1) : 0, w16.Ws16[l], w16.Wn16[l], l > 0)))
             return rc;
         g = a.dH;
         ldg = a.lddh;

@@ -262,7 +262,7 @@ struct Bf16PrepJob {
     uint16_t *dst;
     int64_t ldd;
     int32_t rows, cols;    // of src
-    int32_t dcols;         // plain: columns written per row (cols .. dcols-1 zero)
+    int32_t dcols;         // columns written per row of dst (the ones past the source zero)
     int32_t transpose;     // 1: dst (cols x rows) = bf16(src)^T
     int32_t tiles_c;       // set by prep_bf16
     int64_t first_block;   // set by prep_bf16

@@ -803,7 +803,7 @@ __global__ __launch_bounds__(256) void prep_bf16_kernel(Bf16PrepBatch b) {
 #pragma unroll
         for (int k = 0; k < 32; k += 8) {
             const int c = tc * 32 + ty + k, r = tr * 32 + tx;
-            if (c < J.cols && r < J.rows) J.dst[(int64_t)c * J.ldd + r] = to_bf16(tile[tx][ty + k]);
+            if (c < J.cols && r < J.dcols) J.dst[(int64_t)c * J.ldd + r] = to_bf16(tile[tx][ty + k]);   // (0 past the source)
         }
     } else {
 #pragma unroll
@@ -824,7 +824,7 @@ int prep_bf16(Bf16PrepBatch &b, hipStream_t s) {
         const int wc = J.transpose ? J.cols : J.dcols;
         J.tiles_c = (wc + 31) / 32;
         J.first_block = blocks;
-        blocks += (int64_t)((J.rows + 31) / 32) * J.tiles_c;
+        blocks += (int64_t)(((J.transpose ? J.dcols : J.rows) + 31) / 32) * J.tiles_c;
         bytes += (double)J.rows * J.cols * 4.0 + (double)J.rows * wc * 2.0;
     }
     if (blocks == 0) return GCN_OK;

@@ -938,7 +938,10 @@ enum BigOut {
 };
 // LAYOUT: L_NT (both operands contiguous along k), L_TN (both k-major) or
 // L_NN (A contiguous along k, B k-major).
-template <int OUT, int LAYOUT>
+// TAIL: some K-segment is not a multiple of 32; the 16-byte chunks past its
+// end are read from a chunk of zeros instead, for both operands.
+__device__ __attribute__((aligned(16))) uint16_t g_zero_chunk[8];   // never written
+template <int OUT, int LAYOUT, bool TAIL>
 __global__ __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_eu(2)))
 void gemm_bf16_big_kernel(DevArgs args) {
     constexpr bool KMA = LAYOUT == L_TN, KMB = LAYOUT != L_NT;
@@ -959,6 +962,7 @@ void gemm_bf16_big_kernel(DevArgs args) {
     const uint16_t *const B0 = (const uint16_t *)P.s.B[0], *const B1 = (const uint16_t *)P.s.B[1];
     const int64_t lda0 = P.s.lda[0], lda1 = P.s.lda[1], ldb0 = P.s.ldb[0], ldb1 = P.s.ldb[1];
     const int kt0 = P.s.kt[0];
+    const int K0 = P.s.K[0], K1 = P.s.K[1];
     const int Mlast = P.M - 1, Nlast = P.N - 1;
 
     // Lane `lane` of load q deposits chunk position (wave*Q + q)*64 + lane of
@@ -996,9 +1000,11 @@ void gemm_bf16_big_kernel(DevArgs args) {
         const uint16_t *Bm = s1 ? B1 : B0;
         const int64_t lda = s1 ? lda1 : lda0, ldb = s1 ? ldb1 : ldb0;
         const int k0 = (s1 ? kt - kt0 : kt) * kBigBK;
+        const int left = (s1 ? K1 : K0) - k0;
 #pragma unroll
         for (int q = 0; q < kBigQA; ++q) {
             const uint16_t *g = KMA ? A + (int64_t)(k0 + kmA[q]) * lda + rowA[q] : A + (int64_t)rowA[q] * lda + k0 + chkA[q];
+            if (TAIL && (KMA ? kmA[q] : chkA[q]) >= left) g = g_zero_chunk;
             __builtin_amdgcn_global_load_lds((const void *)g,
                                              (void __attribute__((address_space(3))) *)&lds[stage][(wave * kBigQA + q) * 512],
                                              16, 0, 0);
@@ -1006,6 +1012,7 @@ void gemm_bf16_big_kernel(DevArgs args) {
 #pragma unroll
         for (int q = 0; q < kBigQB; ++q) {
             const uint16_t *g = KMB ? Bm + (int64_t)(k0 + kmB[q]) * ldb + rowB[q] : Bm + (int64_t)rowB[q] * ldb + k0 + chkB[q];
+            if (TAIL && (KMB ? kmB[q] : chkB[q]) >= left) g = g_zero_chunk;
             __builtin_amdgcn_global_load_lds((const void *)g,
                                              (void __attribute__((address_space(3))) *)&lds[stage][kBigStageA + (wave * kBigQB + q) * 512],
                                              16, 0, 0);
@@ -1361,13 +1368,17 @@ int bk_of(int mode) { return mode == 2 ? kBigBK : (mode == 1 ? BK16 : kBK); }
 int tile_m_of(int mode) { return mode == 2 ? kBigT : (mode == 1 ? kTBM16 : (mode == 3 ? 2 * kTBM : kTBM)); }
 int tile_n_of(int mode) { return mode == 2 ? kBigTN : (mode == 1 ? kTBN16 : kTBN); }
 
-// The large-tile bf16 kernel takes NT, TN and NN products whose K-segments
-// are multiples of its k-stage, with 16-byte aligned operand rows; a k-major
+// The large-tile bf16 kernel takes TN products of any K, and NT and NN
+// products whose K-segments are multiples of 8 (an operand with other widths
+// is kept with zero columns up to the next one), with 16-byte aligned operand rows; a k-major
 // operand (A of TN, B of TN and NN) is read in chunks of 8 along M (or N),
 // so its rows must hold M (N) rounded up to 8 (the extra columns only feed
 // outputs that are dropped).
+#ifndef GCN_BIG_NARROW_LO
+#define GCN_BIG_NARROW_LO 32
+#endif
 #ifndef GCN_BIG_NARROW_K
-#define GCN_BIG_NARROW_K 16384
+#define GCN_BIG_NARROW_K 1024
 #endif
 bool big_ok(int layout, int nprob, const GemmProblem *probs) {
     if (GCN_BF16_BIG == 0) return false;
@@ -1379,15 +1390,19 @@ bool big_ok(int layout, int nprob, const GemmProblem *probs) {
         // a tile (the logits of a large subgraph): the product is then bound
         // by its operand and output traffic, not by the idle matrix work.
         // Also for a long-K product (a weight gradient over the subgraph's
-        // vertices), whose split-K blocks fill the GPU whatever the tiles.
+        // vertices), whose split-K blocks fill the GPU whatever the tiles, and
+        // which needs no transposed copies of its operands there: layer
+        // forward + backward, transposed copies / large tile, 8000 vertices
+        // 602 -> 128: 146 / 125 us, 3001 vertices 50 -> 64: 79 / 66 us.
         const int lo = min(probs[i].M, probs[i].N);
         const int64_t tiles = (int64_t)((probs[i].M + kBigT - 1) / kBigT) * ((probs[i].N + kBigTN - 1) / kBigTN);
         const int64_t K = (int64_t)probs[i].seg[0].K + probs[i].seg[1].K;
-        if (lo <= 128 && !(lo >= 64 && (tiles >= GCN_BIG_NARROW_TILES || K >= GCN_BIG_NARROW_K))) return false;
+        if (lo <= 128 && !(lo >= GCN_BIG_NARROW_LO && (tiles >= GCN_BIG_NARROW_TILES || K >= GCN_BIG_NARROW_K))) return false;
         for (int s = 0; s < 2; ++s) {
             const GemmSeg &sg = probs[i].seg[s];
             if (sg.K == 0) continue;
-            if (sg.K % kBigBK || sg.lda % 8 || sg.ldb % 8 || !al(sg.A, 16) || !al(sg.B, 16)) return false;
+            // an operand contiguous along k is read in chunks of 8 k
+            if ((layout != L_TN && sg.K % 8) || sg.lda % 8 || sg.ldb % 8 || !al(sg.A, 16) || !al(sg.B, 16)) return false;
         }
         const int64_t M8 = (probs[i].M + 7) & ~7, N8 = (probs[i].N + 7) & ~7;
         for (int s = 0; s < 2; ++s) {
@@ -1560,6 +1575,14 @@ int gemm(int layout, int nprob, const GemmProblem *probs, int bf16, int split_k,
         partial = (float *)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
     }
     const bool big = bf16 && big_ok(layout, nprob, probs);
+    if (big && split_k > 1) {
+        // one 256 x 256 block per CU: splits that fill whole rounds of the 256
+        // CUs (602 x 128 weight gradients over 8000 vertices, the layer's
+        // backward pass: 300 blocks in two rounds 73 us, 252 in one 62 us)
+        const int64_t t = (int64_t)nprob * ((probs[0].M + kBigT - 1) / kBigT) * ((probs[0].N + kBigTN - 1) / kBigTN);
+        const int64_t rounds = t * split_k / 256;
+        if (rounds >= 1) split_k = (int)std::max<int64_t>(1, 256 * rounds / t);
+    }
     DevArgs a;
     int64_t blocks = 0;
     const int mode = big ? 2 : (bf16 ? 1 : f32_mode(nprob, probs, split_k));
@@ -1612,8 +1635,14 @@ int gemm(int layout, int nprob, const GemmProblem *probs, int bf16, int split_k,
                 any16 = any16 || (a.p[i].split == 1 && probs[i].C16);
             }
             const int out = !any16 ? BIG_F32 : (!any32 ? BIG_B16 : BIG_ALL);
-#define GCN_BIG_LAUNCH(O, LY)                                                                           \
-    if (out == O && layout == LY) hipLaunchKernelGGL((gemm_bf16_big_kernel<O, LY>), grid, dim3(kBigThreads), 0, s, a);
+            bool tail = false;
+            for (int i = 0; i < nprob; ++i)
+                tail = tail || probs[i].seg[0].K % kBigBK || probs[i].seg[1].K % kBigBK;
+#define GCN_BIG_LAUNCH(O, LY)                                                                               \
+    if (out == O && layout == LY) {                                                                         \
+        if (tail) hipLaunchKernelGGL((gemm_bf16_big_kernel<O, LY, true>), grid, dim3(kBigThreads), 0, s, a); \
+        else hipLaunchKernelGGL((gemm_bf16_big_kernel<O, LY, false>), grid, dim3(kBigThreads), 0, s, a);     \
+    }
             GCN_BIG_LAUNCH(BIG_F32, L_NT) GCN_BIG_LAUNCH(BIG_B16, L_NT) GCN_BIG_LAUNCH(BIG_ALL, L_NT)
             GCN_BIG_LAUNCH(BIG_F32, L_TN) GCN_BIG_LAUNCH(BIG_B16, L_TN) GCN_BIG_LAUNCH(BIG_ALL, L_TN)
             GCN_BIG_LAUNCH(BIG_F32, L_NN) GCN_BIG_LAUNCH(BIG_B16, L_NN) GCN_BIG_LAUNCH(BIG_ALL, L_NN)

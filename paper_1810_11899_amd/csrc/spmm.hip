@@ -854,8 +854,10 @@ int spmm_any(bool bf16, int32_t n_rows, int32_t nnz, const int32_t *indptr, IdxR
     const bool sliced = !bf16 && k % 4 == 0 && ldx % 4 == 0 && aligned(X, 16) && ldo % 4 == 0 &&
                         aligned(out, 16) && k >= 128 && (!out16 || (ld16 % 4 == 0 && aligned(out16, 8)));
     // bfloat16 rows on the sliced schedule: whole 8-column lane vectors and
-    // 16-byte aligned rows in and out
-    const bool sliced16 = GCN_SPMM_BF16_SLICED && bf16 && k >= 256 && k % 8 == 0 && ldx % 8 == 0 &&
+    // 16-byte aligned rows in and out, wide enough for two edges per gather to
+    // beat one with a lane per column or two (layer calls, whole: k = 200 at
+    // 50,000 vertices 220 / 185 us, k = 128 at 20,000 80 / 75 us unsliced / sliced)
+    const bool sliced16 = GCN_SPMM_BF16_SLICED && bf16 && k > 64 && k % 8 == 0 && ldx % 8 == 0 &&
                           aligned(X, 16) && (!out || (ldo % 8 == 0 && aligned(out, 16))) &&
                           (!out16 || (ld16 % 8 == 0 && aligned(out16, 16)));
     const double out_bytes = epi == EPI_STORE_BF16 ? 2.0 : (epi == EPI_ACCUMULATE ? 8.0 : 4.0);
