@@ -156,13 +156,13 @@ __device__ __forceinline__ void split3(float x0, float x1, uint32_t &h, uint32_t
 
 // One operand's k-tile, XT rows x 16 k, staged through registers.
 //   KM: element (x, k) sits at ptr[k*ld + x] (contiguous along x): a thread
-//       takes 8 consecutive k of one x, the lanes consecutive x
+//       takes 8 (64-row tiles: 4) consecutive k of one x, the lanes consecutive x
 //   else: at ptr[x*ld + k] (contiguous along k): a thread takes 4 consecutive
 //       k, four lanes a row (16-byte loads at 4-byte alignment: any base and
 //       leading dimension)
 template <bool KM, int XT>
 struct SplitLoader {
-    static constexpr int W = KM ? 8 : 4;                   // k per unit
+    static constexpr int W = KM && XT >= 128 ? 8 : 4;      // k per unit
     static constexpr int NU = XT * kBK / W / kThreads;     // units per thread
     static constexpr int CS = XT * 8 + 64;                 // chunk stride (elements)
     static constexpr int PL = 2 * CS;                      // plane stride
@@ -175,7 +175,7 @@ struct SplitLoader {
         const int v = threadIdx.x + i * kThreads;
         if (KM) {
             x = v % XT;
-            k = (v / XT) * 8;
+            k = (v / XT) * W;
         } else {
             x = v >> 2;
             k = (v & 3) * 4;
@@ -236,7 +236,7 @@ struct SplitLoader {
             uint16_t *d = lds + (k >> 3) * CS + x * 8 + (k & 7);
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
-                if constexpr (KM) *(uint4 *)(d + q * PL) = make_uint4(p[q][0], p[q][1], p[q][2], p[q][3]);
+                if constexpr (W == 8) *(uint4 *)(d + q * PL) = make_uint4(p[q][0], p[q][1], p[q][2], p[q][3]);
                 else *(uint2 *)(d + q * PL) = make_uint2(p[q][0], p[q][1]);
             }
         }
@@ -259,8 +259,9 @@ struct SplitLoader {
 #define GCN_PRIO_UP() __builtin_amdgcn_s_setprio(1)
 #define GCN_PRIO_DOWN() __builtin_amdgcn_s_setprio(0)
 // 2 x 2 wavefronts of FM x FN blocks of 32 x 32: a block tile of 64 FM x 64 FN
+// (256 x 128, 128 x 128 and 64 x 64; f32_mode says which)
 template <int LAYOUT, int FM, int FN>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(FM * FN > 4 ? 2 : 3)))
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(FM * FN > 4 ? 2 : (FM * FN > 1 ? 3 : 4))))
 void gemm_kernel(DevArgs args) {
     constexpr int TBM = 64 * FM, TBN = 64 * FN, WTM = 32 * FM, WTN = 32 * FN;
     using LA = SplitLoader<LAYOUT == L_TN, TBM>;
@@ -422,11 +423,15 @@ void gemm_kernel(DevArgs args) {
     // those rows deposit their accumulator blocks row-major (row stride
     // TBN + 8 floats: the two half-wavefronts' rows, four apart, land 32 banks
     // apart), then all four wavefronts write whole rows, 16 bytes per lane.
-    static_assert(TBN == 128, "epilogue written for a 128-wide tile");
+    static_assert(TBN == 128 || TBN == 64, "a row is half or a quarter of a wavefront's 16-byte stores");
+    constexpr int LR = TBN / 4;             // lanes per row
+    constexpr int RPI = 64 / LR;            // rows per wavefront and store
+    constexpr int NQ = 32 / (4 * RPI);      // stores per pass
+    const int ec = 4 * (lane % LR), er = wave * (NQ * RPI) + lane / LR;   // column, first row of the pass
     constexpr int SLD = TBN + 8;
     static_assert(32 * SLD * 4 <= (int)sizeof(smem), "staging fits the operand buffers");
     float *stg = (float *)smem;
-    const int ecol = n0 + 4 * (lane & 31);
+    const int ecol = n0 + ec;
     float ebv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     if (!to_partial && P.bias)
 #pragma unroll
@@ -435,11 +440,12 @@ void gemm_kernel(DevArgs args) {
     const bool evec = ldd % 4 == 0 && ((uintptr_t)dst & 15) == 0;
     // optional mask operand (a [mask > 0] factor on every stored value), read
     // for a pass's four rows before that pass's barrier; optional column sums
-    // of the stored values over this thread's 16 rows of each 128-row half
+    // of the stored values over this thread's 16 rows of each 128-row half (not
+    // with 64-row tiles)
     const float *const emask = to_partial ? nullptr : P.mask;
     const bool mvec = emask && P.ldm % 4 == 0 && ((uintptr_t)emask & 15) == 0 && ecol + 3 < P.N;
     const bool ecs = !to_partial && P.colpart;
-    float4 mk[4];
+    float4 mk[NQ];
     float cs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     auto put = [&](const floatx16 &v, int jb) {
         const int lc = wn * WTN + jb * 32 + (lane & 31);
@@ -451,8 +457,8 @@ void gemm_kernel(DevArgs args) {
     for (int h = 0; h < 2 * FM; ++h) {
         if (emask) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int row = m0 + 32 * h + wave * 8 + q * 2 + (lane >> 5);
+            for (int q = 0; q < NQ; ++q) {
+                const int row = m0 + 32 * h + er + q * RPI;
                 mk[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                 if (row < P.M && ecol < P.N) {
                     const float *mp = emask + (int64_t)row * P.ldm + ecol;
@@ -472,13 +478,13 @@ void gemm_kernel(DevArgs args) {
             for (int j = 0; j < FN; ++j) put(acc[h % FM][j], j);
         }
         __syncthreads();
-        // rows 32h .. 32h+31 of the tile; a wavefront writes two rows per store
+        // rows 32h .. 32h+31 of the tile; a wavefront writes RPI rows per store
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int lr = wave * 8 + q * 2 + (lane >> 5);
+        for (int q = 0; q < NQ; ++q) {
+            const int lr = er + q * RPI;
             const int row = m0 + 32 * h + lr;
             if (row < P.M && ecol < P.N) {
-                const float4 x = *(const float4 *)&stg[lr * SLD + 4 * (lane & 31)];
+                const float4 x = *(const float4 *)&stg[lr * SLD + ec];
                 float o[4] = {x.x + ebv[0], x.y + ebv[1], x.z + ebv[2], x.w + ebv[3]};
                 if (erelu)
 #pragma unroll
@@ -503,7 +509,7 @@ void gemm_kernel(DevArgs args) {
             }
         }
         __syncthreads();
-        if (ecs && h % 4 == 3) {
+        if (TBM % 128 == 0 && ecs && h % 4 == 3) {
             // a 128-row half is done: the 8 row groups (wavefront, half) of
             // each column, added in order
             const int grp = wave * 2 + (lane >> 5);
@@ -1363,10 +1369,11 @@ bool vec_ok(int layout, const GemmProblem &g, int esz) {
     return true;
 }
 
-// mode 0: float32 kernel; 1: bf16 kernel; 2: bf16 large-tile kernel; 3: float32 kernel, 256-row tiles
+// mode 0: float32 kernel, 128 x 128 tiles; 1: bf16 kernel; 2: bf16 large-tile
+// kernel; 3, 4: float32 kernel, 256 x 128 and 64 x 64 tiles
 int bk_of(int mode) { return mode == 2 ? kBigBK : (mode == 1 ? BK16 : kBK); }
-int tile_m_of(int mode) { return mode == 2 ? kBigT : (mode == 1 ? kTBM16 : (mode == 3 ? 2 * kTBM : kTBM)); }
-int tile_n_of(int mode) { return mode == 2 ? kBigTN : (mode == 1 ? kTBN16 : kTBN); }
+int tile_m_of(int mode) { return mode == 2 ? kBigT : (mode == 1 ? kTBM16 : (mode == 3 ? 2 * kTBM : (mode == 4 ? 64 : kTBM))); }
+int tile_n_of(int mode) { return mode == 2 ? kBigTN : (mode == 1 ? kTBN16 : (mode == 4 ? 64 : kTBN)); }
 
 // The large-tile bf16 kernel takes TN products of any K, and NT and NN
 // products whose K-segments are multiples of 8 (an operand with other widths
@@ -1414,16 +1421,45 @@ bool big_ok(int layout, int nprob, const GemmProblem *probs) {
     return true;
 }
 
-// The float32 tile: 256 x 128 when its blocks still give every CU two (two
-// fit its LDS), 128 x 128 (three per CU) for fewer: a 256 x 128 tile reads a
-// quarter less from LDS per product, but 256 blocks of it leave half of the
-// wavefront slots empty (logits of 65,536 vertices: 143 us on 256 blocks of
-// 256 x 128, 116 us on 512 of 128 x 128; input gradient of the same layer,
-// 2048 blocks against 4096: 660 / 690 us).
-int f32_mode(int nprob, const GemmProblem *probs, int split_k) {
-    const int64_t blocks = (int64_t)nprob * std::max(1, split_k) * ((probs[0].M + 2 * kTBM - 1) / (2 * kTBM)) *
-                           ((probs[0].N + kTBN - 1) / kTBN);
-    return blocks >= 512 ? 3 : 0;
+// The float32 tile, and the splits it needs of the `split_k` planned for
+// 128 x 128 tiles (never more).
+//   - 256 x 128 when its blocks give every CU two (two fit its LDS): it reads a
+//     quarter less from LDS per product than 128 x 128 (three per CU), but 256
+//     blocks of it leave half of the wavefront slots empty (logits of 65,536
+//     vertices: 143 us on 256 blocks of 256 x 128, 116 us on 512 of 128 x 128;
+//     input gradient of the same layer, 2048 blocks against 4096: 660 / 690 us).
+//   - 64 x 64 when 128 x 128 tiles do not give every CU one: four times the
+//     blocks, each k-tile a third of the time, and from 256 of them no split
+//     and no reduce pass.  Whole calls, 128 x 128 split / 64 x 64: 256 -> 128
+//     forward over 8000 vertices 50 / 43 us, 200 -> 128 over 700 38 / 28 us.
+//     (Column sums are kept per 128 rows and need a taller tile.)
+//   - Weight gradients (TN, K = vertices): 64 x 64 tiles and a fourth of the
+//     splits while the product is small enough for their second read of the
+//     operands not to matter: 2^29 multiply-adds (8000 x 256 x 128 both
+//     branches, the layer's backward pass 77 / 74 us; 6205 x 256 x 41, the
+//     head 53 / 45 us; but 8000 x 602 x 128 69 / 74, 16,000 x 300 x 256 75 / 90).
+//     Above that two blocks per CU of few tiles: four, as for many, only add
+//     partials (300 x 256 over 16,000 vertices 88 / 75 us).
+int f32_mode(int layout, int nprob, const GemmProblem *probs, int &split_k) {
+    auto tiles = [&](int tm, int tn) {
+        return (int64_t)nprob * ((probs[0].M + tm - 1) / tm) * ((probs[0].N + tn - 1) / tn);
+    };
+    bool colpart = false;
+    for (int i = 0; i < nprob; ++i) colpart = colpart || probs[i].colpart;
+    const int64_t t128 = tiles(kTBM, kTBN), t64 = tiles(64, 64);
+    auto at_most = [&](int64_t n) { split_k = (int)std::min<int64_t>(split_k, std::max<int64_t>(1, n)); };
+    if (layout == L_TN) {
+        const double madds = (double)nprob * probs[0].M * probs[0].N * ((double)probs[0].seg[0].K + probs[0].seg[1].K);
+        if (!colpart && madds <= (double)(1 << 29)) {
+            at_most(512 / t64);
+            return 4;
+        }
+        if (t128 < 32) at_most(512 / t128);
+    } else if (!colpart && t128 < 256) {
+        at_most(t64 >= 256 ? 1 : 512 / t64);
+        return 4;
+    }
+    return tiles(2 * kTBM, kTBN) * std::max(1, split_k) >= 512 ? 3 : 0;
 }
 
 void fill_dev(int layout, int nprob, const GemmProblem *probs, int bf16, int split_k, float *partial,
@@ -1488,6 +1524,8 @@ void launch(bool vec, int mode, dim3 grid, hipStream_t s, const DevArgs &a) {
             hipLaunchKernelGGL((gemm_bf16_kernel<LAYOUT, true>), grid, dim3(kThreads), 0, s, a);
         else
             hipLaunchKernelGGL((gemm_bf16_kernel<LAYOUT, false>), grid, dim3(kThreads), 0, s, a);
+    } else if (mode == 4) {
+        hipLaunchKernelGGL((gemm_kernel<LAYOUT, 1, 1>), grid, dim3(kThreads), 0, s, a);
     } else if (mode == 3) {
         hipLaunchKernelGGL((gemm_kernel<LAYOUT, 4, 2>), grid, dim3(kThreads), 0, s, a);
     } else {
@@ -1585,7 +1623,7 @@ int gemm(int layout, int nprob, const GemmProblem *probs, int bf16, int split_k,
     }
     DevArgs a;
     int64_t blocks = 0;
-    const int mode = big ? 2 : (bf16 ? 1 : f32_mode(nprob, probs, split_k));
+    const int mode = big ? 2 : (bf16 ? 1 : f32_mode(layout, nprob, probs, split_k));
     fill_dev(layout, nprob, probs, mode, split_k, partial, a, blocks);
     if (blocks == 0) return GCN_OK;
     if (nprob == 2 && (a.p[0].kt_total != a.p[1].kt_total || a.p[0].split != a.p[1].split)) {

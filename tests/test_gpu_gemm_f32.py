@@ -55,11 +55,12 @@ def check(got, a, b, K):
     assert np.all(np.abs(got - ref) <= bound), float((np.abs(got - ref) / (mag + 1e-300)).max())
 
 
-# tile edges (128 / 256 rows, 128 columns, 16 k), remainders, unaligned widths,
-# and row counts whose 256 x 128 tiles number more and fewer than 512
+# tile edges (64 / 128 / 256 rows, 64 / 128 columns, 16 k), remainders,
+# unaligned widths, sizes on both sides of the rules for each tile, and splits
 @pytest.mark.parametrize("n, f, h", [(1, 1, 1), (15, 17, 3), (127, 16, 129), (128, 128, 128), (129, 31, 127),
                                      (257, 33, 130), (300, 602, 41), (5000, 50, 64), (66000, 40, 260),
-                                     (131072 + 77, 20, 20)])
+                                     (131072 + 77, 20, 20), (63, 65, 64), (64, 64, 63), (65, 63, 65), (8191, 256, 130),
+                                     (16400, 300, 120), (1000, 1030, 190), (33000, 70, 65)])
 def test_products_at_tile_edges(n, f, h):
     rg = np.random.default_rng(n + f + h)
     H = rg.standard_normal((n, f), dtype=np.float32) * np.exp2(rg.integers(-12, 12, (n, f))).astype(np.float32)
