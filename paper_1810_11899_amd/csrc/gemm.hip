@@ -629,21 +629,21 @@ struct TileLoader16 {
 // a bfloat16 value (raw bits) compares > 0 exactly when its float32 widening does
 __device__ __forceinline__ bool bf16_bits_positive(uint32_t b) { return __uint_as_float(b << 16) > 0.0f; }
 
-template <int LAYOUT, bool VEC>
+// 2 x 2 wavefronts of FM x FN blocks of 32 x 32
+template <int LAYOUT, bool VEC, int FM, int FN>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(GCN_BF16_WAVES_PER_EU)))
 void gemm_bf16_kernel(DevArgs args) {
     constexpr bool A_KMAJOR = (LAYOUT == L_TN);
     constexpr bool B_KMAJOR = (LAYOUT != L_NT);
-    constexpr int WTM = kTBM16 / 2, WTN = kTBN16 / 2;
-    constexpr int FM = WTM / 32, FN = WTN / 32;
-    __shared__ __attribute__((aligned(16))) uint16_t As[2][kTBM16][LDK16];
-    __shared__ __attribute__((aligned(16))) uint16_t Bs[2][kTBN16][LDK16];
+    constexpr int WTM = 32 * FM, WTN = 32 * FN, TBM = 2 * WTM, TBN = 2 * WTN;
+    __shared__ __attribute__((aligned(16))) uint16_t As[2][TBM][LDK16];
+    __shared__ __attribute__((aligned(16))) uint16_t Bs[2][TBN][LDK16];
 
     BlockCoord bc;
     if (!decode_block(args, bc)) return;
     const DevProblem &P = args.p[bc.pi];
     const int split = bc.split;
-    const int m0 = bc.tm * kTBM16, n0 = bc.tn * kTBN16;
+    const int m0 = bc.tm * TBM, n0 = bc.tn * TBN;
     const int kt_begin = split * P.kt_per_split;
     int kt_end = kt_begin + P.kt_per_split;
     if (kt_end > P.kt_total) kt_end = P.kt_total;
@@ -652,8 +652,8 @@ void gemm_bf16_kernel(DevArgs args) {
     const int wave = threadIdx.x >> 6;
     const int wm = wave >> 1, wn = wave & 1;
 
-    TileLoader16<A_KMAJOR, VEC, kTBM16> la;
-    TileLoader16<B_KMAJOR, VEC, kTBN16> lb;
+    TileLoader16<A_KMAJOR, VEC, TBM> la;
+    TileLoader16<B_KMAJOR, VEC, TBN> lb;
     auto load = [&](int kt) {
         const int sg = kt < P.s.kt[0] ? 0 : 1;
         const int kk = (sg == 0 ? kt : kt - P.s.kt[0]) * BK16;
@@ -733,20 +733,19 @@ void gemm_bf16_kernel(DevArgs args) {
                 }
             }
         }
-    if (ecs) {
+    if (TBM == 128 && ecs) {   // column-sum rows are 128-row tiles
         // the 4 row groups (wavefront row, half) of each column, in order
-        static_assert(kTBM16 == 128, "column-sum rows are 128-row tiles");
         float *red = (float *)&As[0][0][0];
-        static_assert(4 * kTBN16 * sizeof(float) <= sizeof(As), "column sums fit the operand buffer");
+        static_assert(4 * TBN * sizeof(float) <= sizeof(As), "column sums fit the operand buffer");
         __syncthreads();   // operand reads done
         const int grp = wm * 2 + (lane >> 5);
 #pragma unroll
-        for (int j = 0; j < FN; ++j) red[grp * kTBN16 + wn * WTN + j * 32 + (lane & 31)] = cs[j];
+        for (int j = 0; j < FN; ++j) red[grp * TBN + wn * WTN + j * 32 + (lane & 31)] = cs[j];
         __syncthreads();
-        if (threadIdx.x < kTBN16) {
+        if (threadIdx.x < TBN) {
             float t = 0.0f;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) t += red[g * kTBN16 + threadIdx.x];
+            for (int g = 0; g < 4; ++g) t += red[g * TBN + threadIdx.x];
             const int col = n0 + (int)threadIdx.x;
             if (col < P.N) P.colpart[(int64_t)bc.tm * P.N + col] = t;
         }
@@ -1370,10 +1369,10 @@ bool vec_ok(int layout, const GemmProblem &g, int esz) {
 }
 
 // mode 0: float32 kernel, 128 x 128 tiles; 1: bf16 kernel; 2: bf16 large-tile
-// kernel; 3, 4: float32 kernel, 256 x 128 and 64 x 64 tiles
-int bk_of(int mode) { return mode == 2 ? kBigBK : (mode == 1 ? BK16 : kBK); }
-int tile_m_of(int mode) { return mode == 2 ? kBigT : (mode == 1 ? kTBM16 : (mode == 3 ? 2 * kTBM : (mode == 4 ? 64 : kTBM))); }
-int tile_n_of(int mode) { return mode == 2 ? kBigTN : (mode == 1 ? kTBN16 : (mode == 4 ? 64 : kTBN)); }
+// kernel; 3, 4: float32 kernel, 256 x 128 and 64 x 64 tiles; 5: bf16 kernel, 64 x 64 tiles
+int bk_of(int mode) { return mode == 2 ? kBigBK : (mode == 1 || mode == 5 ? BK16 : kBK); }
+int tile_m_of(int mode) { return mode == 2 ? kBigT : (mode == 1 ? kTBM16 : (mode == 3 ? 2 * kTBM : (mode >= 4 ? 64 : kTBM))); }
+int tile_n_of(int mode) { return mode == 2 ? kBigTN : (mode == 1 ? kTBN16 : (mode >= 4 ? 64 : kTBN)); }
 
 // The large-tile bf16 kernel takes TN products of any K, and NT and NN
 // products whose K-segments are multiples of 8 (an operand with other widths
@@ -1462,6 +1461,24 @@ int f32_mode(int layout, int nprob, const GemmProblem *probs, int &split_k) {
     return tiles(2 * kTBM, kTBN) * std::max(1, split_k) >= 512 ? 3 : 0;
 }
 
+// The bfloat16 kernel's tile, by the same reasoning: 64 x 64 for products of
+// under 256 tiles of 128 x 128, and for weight gradients (K = vertices, TN or
+// NT on transposed copies) of up to 2^29 multiply-adds.  Whole calls, 128 x 128
+// / 64 x 64: sigmoid head, 16,000 vertices 103 / 90 us; 50 -> 64 forward, 3001
+// vertices 43 / 32 us; 200 -> 64 backward, 1000 vertices 56 / 53 us.
+int bf16_mode(int layout, int nprob, const GemmProblem *probs, int &split_k) {
+    auto tiles = [&](int t) { return (int64_t)nprob * ((probs[0].M + t - 1) / t) * ((probs[0].N + t - 1) / t); };
+    for (int i = 0; i < nprob; ++i)
+        if (probs[i].colpart) return 1;
+    const int64_t t64 = tiles(64);
+    const double K = (double)probs[0].seg[0].K + probs[0].seg[1].K;
+    const bool long_k = layout == L_TN || K > 4.0 * std::max(probs[0].M, probs[0].N);
+    if (long_k ? (double)nprob * probs[0].M * probs[0].N * K > (double)(1 << 29) : tiles(128) >= 256) return 1;
+    const int64_t most = !long_k && t64 >= 256 ? 1 : std::max<int64_t>(1, 512 / t64);
+    split_k = (int)std::min<int64_t>(split_k, most);
+    return 5;
+}
+
 void fill_dev(int layout, int nprob, const GemmProblem *probs, int bf16, int split_k, float *partial,
               DevArgs &a, int64_t &blocks) {
     const int BK = bk_of(bf16);  // bf16 here is the kernel mode (0, 1, 2)
@@ -1521,9 +1538,14 @@ template <int LAYOUT>
 void launch(bool vec, int mode, dim3 grid, hipStream_t s, const DevArgs &a) {
     if (mode == 1) {
         if (vec)
-            hipLaunchKernelGGL((gemm_bf16_kernel<LAYOUT, true>), grid, dim3(kThreads), 0, s, a);
+            hipLaunchKernelGGL((gemm_bf16_kernel<LAYOUT, true, 2, 2>), grid, dim3(kThreads), 0, s, a);
         else
-            hipLaunchKernelGGL((gemm_bf16_kernel<LAYOUT, false>), grid, dim3(kThreads), 0, s, a);
+            hipLaunchKernelGGL((gemm_bf16_kernel<LAYOUT, false, 2, 2>), grid, dim3(kThreads), 0, s, a);
+    } else if (mode == 5) {
+        if (vec)
+            hipLaunchKernelGGL((gemm_bf16_kernel<LAYOUT, true, 1, 1>), grid, dim3(kThreads), 0, s, a);
+        else
+            hipLaunchKernelGGL((gemm_bf16_kernel<LAYOUT, false, 1, 1>), grid, dim3(kThreads), 0, s, a);
     } else if (mode == 4) {
         hipLaunchKernelGGL((gemm_kernel<LAYOUT, 1, 1>), grid, dim3(kThreads), 0, s, a);
     } else if (mode == 3) {
@@ -1623,7 +1645,7 @@ int gemm(int layout, int nprob, const GemmProblem *probs, int bf16, int split_k,
     }
     DevArgs a;
     int64_t blocks = 0;
-    const int mode = big ? 2 : (bf16 ? 1 : f32_mode(layout, nprob, probs, split_k));
+    const int mode = big ? 2 : (bf16 ? bf16_mode(layout, nprob, probs, split_k) : f32_mode(layout, nprob, probs, split_k));
     fill_dev(layout, nprob, probs, mode, split_k, partial, a, blocks);
     if (blocks == 0) return GCN_OK;
     if (nprob == 2 && (a.p[0].kt_total != a.p[1].kt_total || a.p[0].split != a.p[1].split)) {
