@@ -236,12 +236,15 @@ GemmProblem dw_problem(int32_t f_in, int32_t h, int32_t n) {
     return g;
 }
 
-LayerPlan plan_layer(int32_t n, int32_t nnz, int32_t f_in, int32_t h, int order, bool dH, int prec) {
+// w_ready: the model step converted the layer's weights up front and holds the
+// columns' padding with them, so the call's own (then unread) region has none
+LayerPlan plan_layer(int32_t n, int32_t nnz, int32_t f_in, int32_t h, int order, bool dH, int prec,
+                     bool w_ready = false) {
     LayerPlan p{};
     p.need_G = bwd_uses_G(order, dH, f_in, h);
     p.bf16 = prec == GCN_BF16;
     const size_t E = p.bf16 ? 2 : 4;  // bytes per stored intermediate element
-    const size_t W16 = p.bf16 ? 2 * align256((size_t)pad8(f_in) * h * 2) : 0;
+    const size_t W16 = p.bf16 ? 2 * align256((size_t)(w_ready ? f_in : pad8(f_in)) * h * 2) : 0;
     // bfloat16 products run with both operands contiguous along K: the
     // backward also keeps P^T (and dZ_n^T for aggregate-first with G)
     p.bwd_PT = p.bf16 ? align256((size_t)n * 2 * h * 2) : 0;
@@ -487,7 +490,7 @@ static int layer_fwd(bool launch, const gcn_csr *A, const float *H, int32_t f_in
     const size_t sneed = saved_bytes(n, f_in, h, order, prec);
     REQUIRE(saved_bytes_ >= sneed && (sneed == 0 || saved), GCN_EWORKSPACE,
             "gcn_layer_fwd: saved buffer %zu < %zu bytes", saved_bytes_, sneed);
-    const LayerPlan pl = plan_layer(n, A->nnz, f_in, h, order, true, prec);
+    const LayerPlan pl = plan_layer(n, A->nnz, f_in, h, order, true, prec, lk.WsT != nullptr);
     REQUIRE(ws && ws_bytes >= pl.fwd_total, GCN_EWORKSPACE, "gcn_layer_fwd: workspace %zu < %zu bytes",
             ws_bytes, pl.fwd_total);
     if (!launch) return GCN_OK;
@@ -504,8 +507,8 @@ static int layer_fwd(bool launch, const gcn_csr *A, const float *H, int32_t f_in
         uint16_t *H16T = (uint16_t *)((char *)saved + one);
         uint16_t *AGG16 = af ? (uint16_t *)((char *)saved + 2 * one) : nullptr;
         uint16_t *AGG16T = af ? (uint16_t *)((char *)saved + 3 * one) : nullptr;
-        uint16_t *WsT = ar.take<uint16_t>((size_t)pad8(f_in) * h);
-        uint16_t *WnT = ar.take<uint16_t>((size_t)pad8(f_in) * h);
+        uint16_t *WsT = lk.WsT ? const_cast<uint16_t *>(lk.WsT) : ar.take<uint16_t>((size_t)pad8(f_in) * h);
+        uint16_t *WnT = lk.WsT ? const_cast<uint16_t *>(lk.WnT) : ar.take<uint16_t>((size_t)pad8(f_in) * h);
         // H16 (and H16T for the transposed weight-gradient products) in one
         // pass over H, unless the layer below wrote them
         const bool tnw = bf16_dw_rowmajor(n, f_in, h, lk.in_ready);
@@ -515,10 +518,7 @@ static int layer_fwd(bool launch, const gcn_csr *A, const float *H, int32_t f_in
                      : transpose_bf16_copy(n, f_in, H, 0, ldh, H16T, n, H16, f_in, s);
             if (rc) return rc;
         }
-        if (lk.WsT) {
-            WsT = const_cast<uint16_t *>(lk.WsT);
-            WnT = const_cast<uint16_t *>(lk.WnT);
-        } else {
+        if (!lk.WsT) {
             Bf16PrepBatch wb;
             wb.add(W_self, h, f_in, h, WsT, fp, fp, true);
             wb.add(W_neigh, h, f_in, h, WnT, fp, fp, true);
@@ -653,7 +653,7 @@ static int layer_bwd(bool launch, const gcn_csr *A, const gcn_csr *AT, const flo
     REQUIRE(!dz_ready || n > 0, GCN_EINVAL, "gcn_layer_bwd: masked dY needs n > 0");
     REQUIRE(!below_dbias || (want_dH && dH_mask_fusable(n, f_in, h, order, prec)), GCN_EINVAL,
             "gcn_layer_bwd: the masked input gradient needs an unsplit product");
-    const LayerPlan pl = plan_layer(n, A->nnz, f_in, h, order, want_dH, prec);
+    const LayerPlan pl = plan_layer(n, A->nnz, f_in, h, order, want_dH, prec, Ws16_ready != nullptr);
     REQUIRE(ws && ws_bytes >= pl.bwd_total, GCN_EWORKSPACE, "gcn_layer_bwd: workspace %zu < %zu bytes",
             ws_bytes, pl.bwd_total);
     if (!launch) return GCN_OK;
@@ -1133,14 +1133,18 @@ size_t gcn_model_workspace_bytes(int32_t n, int32_t nnz, int32_t L, const gcn_la
                                  const gcn_head_args *head, gcn_prec prec) {
     if (n < 0 || nnz < 0 || L < 1 || !layers) return 0;
     size_t b = 0;
-    for (int32_t l = 0; l < L; ++l)
-        b = std::max(b, plan_layer(n, nnz, layers[l].f_in, layers[l].h, layers[l].order, true, prec).total);
+    const size_t w16 = model_w16_bytes(n, L, layers, head, prec);
+    for (int32_t l = 0; l < L; ++l) {
+        // a first layer without an input gradient has no W rows converted: its
+        // backward call then reads no weights, and plans no region for them
+        const gcn_layer_args &a = layers[l];
+        b = std::max(b, plan_layer(n, nnz, a.f_in, a.h, a.order, true, prec, w16 != 0).total);
+    }
     if (head) b = std::max(b, plan_loss(n, 2 * layers[L - 1].h, head->C, prec).total);
     // the row ranges of A and A^T, shared by the calls, and with bfloat16
     // operands the last layer's output as the head's bfloat16 rows and
     // transposed rows
-    return b + 2 * spmm_bounds_bytes(n, nnz) + model_hl16_bytes(n, L, layers, head, prec) +
-           model_w16_bytes(n, L, layers, head, prec);
+    return b + 2 * spmm_bounds_bytes(n, nnz) + model_hl16_bytes(n, L, layers, head, prec) + w16;
 }
 
 namespace {
