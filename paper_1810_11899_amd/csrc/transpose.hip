@@ -3,176 +3,208 @@
 // Row j of A^T lists the rows i of A that hold column j, in ascending i, with
 // equal entries in their CSR order.  The CSR entries are already in row-major
 // order, so A^T is exactly a *stable* sort of the entries by column.  This is
-// done as an LSD radix sort of (key = column, value = entry position p) with
-// 8-bit digits:
+// done as an LSD radix sort with digits of up to 9 bits (two passes up to
+// 262,144 columns), whose payload is what the output holds: the entry's row
+// and value (bit for bit), so that the last pass writes t_indices and t_vals.
+// Per pass:
 //   1. per-tile digit histograms (integer LDS atomics: counts do not depend on
 //      the order of the increments);
-//   2. one exclusive scan over (digit, tile) in digit-major order;
-//   3. a stable scatter: each tile walks its keys in order, 256 at a time, and
-//      ranks equal digits with wavefront ballots (lane order) and per-wavefront
-//      counts (wavefront order), so every key lands at a position that only
-//      depends on the input.
-// Then t_indptr[j] = lower_bound(sorted keys, j), and each output entry looks
-// up its source row (upper_bound of p in indptr, minus one) and copies vals[p]
-// bit for bit.  The integer output is unique, hence bit-exact.
+//   2. per digit, an exclusive scan over the tiles and the digit's total;
+//   3. a stable scatter: each wavefront ranks its part of the tile in order
+//      with ballots (lane order) and running counts, the tile is sorted by
+//      digit in LDS, and every digit's run is written as one piece.  Every key
+//      lands at a position that only depends on the input.
+// Then t_indptr[j] = lower_bound(sorted keys, j).  The integer output is
+// unique, hence bit-exact.
+//
+// What bounds it: the passes move 12 bytes an entry in and out (2 M entries:
+// 48 MB a pass), and a 2048-key tile scattered key by key wrote 4-byte pieces
+// and gathered rows and values at the end (50,000 columns, 2 M entries: 151
+// us; 4096-key tiles, sorted, with their payload: 70 us).
+#include <algorithm>
+
 #include "common.h"
 
 namespace gcn {
 namespace {
 
 constexpr int kTB = 256;            // threads per tile block
-constexpr int kItems = 8;           // keys per thread per tile
+constexpr int kItems = 16;          // keys per thread per tile
 constexpr int kTile = kTB * kItems; // keys per tile
-constexpr int kRadix = 256;
+constexpr int kDigitBits = 9;       // digits of at most this many bits
+constexpr int kRadix = 1 << kDigitBits;
+constexpr int kWaves = kTB / 64;
 
-__global__ __launch_bounds__(kTB) void iota_kernel(int32_t nnz, IdxRef indices,
-                                                   uint32_t *__restrict__ keys, int32_t *__restrict__ vals) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < nnz; p += stride) {
-        keys[p] = (uint32_t)indices[p];
-        vals[p] = (int32_t)p;
-    }
-}
-
-__global__ __launch_bounds__(kTB) void hist_kernel(int32_t nnz, const uint32_t *__restrict__ keys, int shift,
-                                                   int32_t ntiles, int32_t *__restrict__ hist) {
+// the keys of a pass: A's column indices (first pass) or the last pass's keys
+__global__ __launch_bounds__(kTB) void hist_kernel(int32_t nnz, IdxRef first, const uint32_t *__restrict__ keys,
+                                                   int shift, uint32_t mask, int32_t ntiles,
+                                                   int32_t *__restrict__ hist) {
     __shared__ int32_t cnt[kRadix];
-    cnt[threadIdx.x] = 0;
+    for (int d = threadIdx.x; d < kRadix; d += kTB) cnt[d] = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * kTile;
+    uint32_t k[kItems];
+#pragma unroll
     for (int it = 0; it < kItems; ++it) {
-        const int64_t p = base + it * kTB + threadIdx.x;
-        if (p < nnz) atomicAdd(&cnt[(keys[p] >> shift) & 0xFF], 1);
+        const int64_t p = min(base + it * kTB + (int64_t)threadIdx.x, (int64_t)nnz - 1);
+        k[it] = keys ? keys[p] : (uint32_t)first[p];
     }
-    __syncthreads();
-    hist[(int64_t)threadIdx.x * ntiles + blockIdx.x] = cnt[threadIdx.x];
-}
-
-// Exclusive scan of `len` ints in three phases: per-segment sums, a scan of
-// the segment sums (one block), and a per-segment scan plus its offset.
-// Integer sums, so the result does not depend on the schedule.
-constexpr int kScanPer = 16;                   // ints per thread
-constexpr int kScanSeg = kTB * kScanPer;       // ints per block segment
-
-__global__ __launch_bounds__(kTB) void scan_reduce_kernel(int64_t len, const int32_t *__restrict__ in,
-                                                          int32_t *__restrict__ seg_sums) {
-    __shared__ int32_t sh[kTB];
-    const int64_t base = (int64_t)blockIdx.x * kScanSeg;
-    int32_t s = 0;
-    for (int i = 0; i < kScanPer; ++i) {
-        const int64_t e = base + (int64_t)i * kTB + threadIdx.x;
-        if (e < len) s += in[e];
-    }
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = kTB / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) seg_sums[blockIdx.x] = sh[0];
-}
-
-// exclusive scan of a short array by one block of 1024 threads
-__global__ __launch_bounds__(1024) void scan_small_kernel(int64_t len, const int32_t *__restrict__ in,
-                                                          int32_t *__restrict__ out) {
-    __shared__ int32_t sh[1024];
-    const int t = threadIdx.x;
-    const int64_t per = (len + 1023) / 1024;
-    const int64_t b = t * per;
-    const int64_t e = b + per < len ? b + per : len;
-    int32_t s = 0;
-    for (int64_t i = b; i < e; ++i) s += in[i];
-    sh[t] = s;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-        const int32_t v = t >= o ? sh[t - o] : 0;
-        __syncthreads();
-        sh[t] += v;
-        __syncthreads();
-    }
-    int32_t run = sh[t] - s;
-    for (int64_t i = b; i < e; ++i) {
-        const int32_t v = in[i];
-        out[i] = run;
-        run += v;
-    }
-}
-
-__global__ __launch_bounds__(kTB) void scan_down_kernel(int64_t len, const int32_t *__restrict__ in,
-                                                        const int32_t *__restrict__ seg_offs,
-                                                        int32_t *__restrict__ out) {
-    __shared__ int32_t sh[kTB];
-    const int t = threadIdx.x;
-    const int64_t base = (int64_t)blockIdx.x * kScanSeg + (int64_t)t * kScanPer;
-    int32_t v[kScanPer];
-    int32_t s = 0;
 #pragma unroll
-    for (int i = 0; i < kScanPer; ++i) {
-        v[i] = base + i < len ? in[base + i] : 0;
-        s += v[i];
-    }
-    sh[t] = s;
+    for (int it = 0; it < kItems; ++it)
+        if (base + it * kTB + threadIdx.x < nnz) atomicAdd(&cnt[(k[it] >> shift) & mask], 1);
     __syncthreads();
-    for (int o = 1; o < kTB; o <<= 1) {
-        const int32_t x = t >= o ? sh[t - o] : 0;
-        __syncthreads();
-        sh[t] += x;
-        __syncthreads();
-    }
-    int32_t run = seg_offs[blockIdx.x] + sh[t] - s;
-#pragma unroll
-    for (int i = 0; i < kScanPer; ++i) {
-        if (base + i < len) out[base + i] = run;
-        run += v[i];
-    }
+    for (uint32_t d = threadIdx.x; d <= mask; d += kTB) hist[(int64_t)d * ntiles + blockIdx.x] = cnt[d];
 }
 
-__global__ __launch_bounds__(kTB) void scatter_kernel(int32_t nnz, const uint32_t *__restrict__ keys_in,
-                                                      const int32_t *__restrict__ vals_in, int shift,
+// exclusive scan over the block of one value per thread; total: their sum
+__device__ __forceinline__ int32_t block_scan(int32_t x, int32_t *sh, int32_t &total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int32_t incl = x;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int32_t y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+    }
+    if (lane == 63) sh[wave] = incl;
+    __syncthreads();
+    int32_t before = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        if (w < wave) before += sh[w];
+        total += sh[w];
+    }
+    __syncthreads();
+    return before + incl - x;
+}
+
+// one block per digit: its counts per tile become their exclusive scan, in
+// place; total[d] = their sum
+__global__ __launch_bounds__(kTB) void scan_tiles_kernel(int32_t ntiles, int32_t *__restrict__ hist,
+                                                         int32_t *__restrict__ total) {
+    __shared__ int32_t sh[kWaves];
+    int32_t *h = hist + (int64_t)blockIdx.x * ntiles;
+    int32_t carry = 0;
+    for (int32_t t0 = 0; t0 < ntiles; t0 += 4 * kTB) {
+        const int32_t t = t0 + 4 * (int32_t)threadIdx.x;
+        int32_t v[4], sum = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            v[e] = t + e < ntiles ? h[t + e] : 0;
+            sum += v[e];
+        }
+        int32_t all;
+        int32_t run = carry + block_scan(sum, sh, all);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (t + e < ntiles) h[t + e] = run;
+            run += v[e];
+        }
+        carry += all;
+    }
+    if (threadIdx.x == 0) total[blockIdx.x] = carry;
+}
+
+// A pass takes the payload as two arrays (rows, vals: A's, or an earlier
+// pass's t_indices and t_vals) or as pairs, and leaves it as the other form,
+// so that a pass never reads what it writes and the last one ends in
+// t_indices and t_vals.
+template <bool IN_PAIRS>
+__global__ __launch_bounds__(kTB) void scatter_kernel(int32_t nnz, IdxRef first, const uint32_t *__restrict__ keys_in,
+                                                      const int32_t *__restrict__ rows,
+                                                      const float *__restrict__ vals,
+                                                      const uint2 *__restrict__ pairs_in, int shift, int dbits,
                                                       int32_t ntiles, const int32_t *__restrict__ offs,
-                                                      uint32_t *__restrict__ keys_out,
-                                                      int32_t *__restrict__ vals_out) {
-    __shared__ int32_t run[kRadix];          // keys of each digit placed so far by this tile
-    __shared__ int32_t wcnt[kTB / 64][kRadix];
+                                                      const int32_t *__restrict__ total,
+                                                      uint32_t *__restrict__ keys_out, uint2 *__restrict__ pairs_out,
+                                                      int32_t *__restrict__ t_indices, float *__restrict__ t_vals) {
+    __shared__ uint32_t skey[kTile];
+    __shared__ uint2 spay[kTile];
+    __shared__ int32_t cnt[kWaves][kRadix];   // a wavefront's keys of each digit, then where its next one goes
+    __shared__ int32_t gbase[kRadix];         // a digit's first output minus its first place in the tile
+    __shared__ int32_t sh[kWaves];
     const int t = threadIdx.x;
     const int lane = t & 63, wave = t >> 6;
-    run[t] = offs[(int64_t)t * ntiles + blockIdx.x];
-    const int64_t base = (int64_t)blockIdx.x * kTile;
-    const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    for (int it = 0; it < kItems; ++it) {
-        for (int w = 0; w < kTB / 64; ++w) wcnt[w][t] = 0;
-        __syncthreads();
-        const int64_t p = base + it * kTB + t;
-        const bool valid = p < nnz;
-        uint32_t key = 0;
-        int32_t val = 0;
-        int digit = 0;
-        if (valid) {
-            key = keys_in[p];
-            val = vals_in[p];
-            digit = (key >> shift) & 0xFF;
-        }
-        // lanes of this wavefront holding the same digit
-        unsigned long long match = __ballot(valid);
+    const uint32_t mask = (1u << dbits) - 1u;
+    const int64_t base = (int64_t)blockIdx.x * kTile + wave * (64 * kItems);
+    const int32_t count = (int32_t)min((int64_t)kTile, (int64_t)nnz - (int64_t)blockIdx.x * kTile);
+    uint32_t key[kItems];
+    uint2 pay[kItems];
 #pragma unroll
-        for (int bit = 0; bit < 8; ++bit) {
-            const unsigned long long bb = __ballot((digit >> bit) & 1);
-            match &= ((digit >> bit) & 1) ? bb : ~bb;
+    for (int it = 0; it < kItems; ++it) {
+        const int64_t p = min(base + it * 64 + lane, (int64_t)nnz - 1);
+        key[it] = keys_in ? keys_in[p] : (uint32_t)first[p];
+        pay[it] = IN_PAIRS ? pairs_in[p] : make_uint2((uint32_t)rows[p], __float_as_uint(vals[p]));
+    }
+    for (int d = t; d < kWaves * kRadix; d += kTB) (&cnt[0][0])[d] = 0;
+    __syncthreads();
+    const uint64_t below = (1ull << lane) - 1ull;
+    int32_t rank[kItems];   // among the wavefront's keys of the same digit
+#pragma unroll
+    for (int it = 0; it < kItems; ++it) {
+        const bool valid = base + it * 64 + lane < nnz;
+        const uint32_t digit = (key[it] >> shift) & mask;
+        uint64_t match = __ballot(valid);
+        for (int bit = 0; bit < dbits; ++bit) {
+            const uint64_t bb = __ballot((digit >> bit) & 1u);
+            match &= ((digit >> bit) & 1u) ? bb : ~bb;
         }
-        const int wrank = __popcll(match & below);
-        if (valid && wrank == 0) wcnt[wave][digit] = __popcll(match);
-        __syncthreads();
-        if (valid) {
-            int pos = run[digit] + wrank;
-            for (int w = 0; w < wave; ++w) pos += wcnt[w][digit];
-            keys_out[pos] = key;
-            vals_out[pos] = val;
+        const int32_t seen = valid ? cnt[wave][digit] : 0;
+        rank[it] = seen + (int32_t)__popcll(match & below);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // every lane has read its count
+        if (valid && (match & below) == 0) cnt[wave][digit] = seen + (int32_t)__popcll(match);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    __syncthreads();
+    // thread t: digits 2t and 2t + 1 (in order over the block)
+    {
+        int32_t c[2], g[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const uint32_t d = 2 * t + e;
+            c[e] = 0;
+            for (int w = 0; w < kWaves; ++w) {
+                const int32_t x = cnt[w][d];
+                cnt[w][d] = c[e];
+                c[e] += x;
+            }
+            g[e] = d <= mask ? total[d] : 0;
         }
-        __syncthreads();
-        int32_t add = 0;
-        for (int w = 0; w < kTB / 64; ++w) add += wcnt[w][t];
-        run[t] += add;
-        __syncthreads();
+        int32_t all;
+        const int32_t l0 = block_scan(c[0] + c[1], sh, all);
+        const int32_t g0 = block_scan(g[0] + g[1], sh, all);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const uint32_t d = 2 * t + e;
+            const int32_t l = l0 + (e ? c[0] : 0);
+            for (int w = 0; w < kWaves; ++w) cnt[w][d] += l;
+            if (d <= mask) gbase[d] = g0 + (e ? g[0] : 0) + offs[(int64_t)d * ntiles + blockIdx.x] - l;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < kItems; ++it)
+        if (base + it * 64 + lane < nnz) {
+            const int32_t pos = cnt[wave][(key[it] >> shift) & mask] + rank[it];
+            skey[pos] = key[it];
+            spay[pos] = pay[it];
+        }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < kItems; ++it) {
+        const int32_t i = it * kTB + t;
+        if (i < count) {
+            const uint32_t k = skey[i];
+            const uint2 x = spay[i];
+            const int64_t q = (int64_t)gbase[(k >> shift) & mask] + i;
+            keys_out[q] = k;
+            if (!pairs_out) {
+                t_indices[q] = (int32_t)x.x;
+                t_vals[q] = __uint_as_float(x.y);
+            } else {
+                pairs_out[q] = x;
+            }
+        }
     }
 }
 
@@ -197,20 +229,6 @@ __global__ __launch_bounds__(kTB) void rowid_kernel(int32_t n_rows, const int32_
     if (r >= n_rows) return;
     const int32_t b = indptr[r], e = indptr[r + 1];
     for (int32_t p = b + (int32_t)(threadIdx.x & 63); p < e; p += 64) rowid[p] = (int32_t)r;
-}
-
-// t_indices[q] = row of entry perm[q] in A;  t_vals[q] = vals[perm[q]]
-__global__ __launch_bounds__(kTB) void finalize_kernel(int32_t nnz, const int32_t *__restrict__ rowid,
-                                                       const float *__restrict__ vals,
-                                                       const int32_t *__restrict__ perm,
-                                                       int32_t *__restrict__ t_indices,
-                                                       float *__restrict__ t_vals) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < nnz; q += stride) {
-        const int32_t p = perm[q];
-        t_indices[q] = rowid[p];
-        t_vals[q] = vals[p];
-    }
 }
 
 // Symmetric pattern: A^T has A's row pointers and indices; the value at
@@ -327,17 +345,32 @@ int key_bits(int32_t n_cols) {
 
 }  // namespace
 
+namespace {
+// Arrays of a sort: keys twice (the second first holds the entries' rows) and
+// (row, value) pairs once.
+struct SortPlan {
+    int passes, dbits;
+    int32_t ntiles;
+};
+SortPlan sort_plan(int32_t n_cols, int32_t nnz) {
+    SortPlan p;
+    const int bits = std::max(1, key_bits(n_cols));
+    p.ntiles = (int32_t)(((int64_t)nnz + kTile - 1) / kTile);
+    // a single tile counts at most 256 digits: a workspace of no more than 16
+    // bytes an entry and 3 KB also for a few entries
+    const int most = p.ntiles == 1 ? 8 : kDigitBits;
+    p.passes = (bits + most - 1) / most;
+    p.dbits = (bits + p.passes - 1) / p.passes;
+    return p;
+}
+}  // namespace
+
 size_t transpose_workspace_bytes(int32_t n_rows, int32_t n_cols, int32_t nnz) {
     (void)n_rows;
-    (void)n_cols;
-    const int64_t ntiles = ((int64_t)nnz + kTile - 1) / kTile;
-    size_t b = 0;
-    b += 2 * align256((size_t)nnz * 4);          // keys ping-pong
-    b += 2 * align256((size_t)nnz * 4);          // values ping-pong
-    b += 2 * align256((size_t)ntiles * kRadix * 4);  // hist, offsets
-    const int64_t segs = (ntiles * kRadix + kScanSeg - 1) / kScanSeg;
-    b += 2 * align256((size_t)(segs + 1) * 4);        // segment sums, segment offsets
-    return b + 256;
+    if (nnz <= 0) return 256;
+    const SortPlan p = sort_plan(n_cols, nnz);
+    return 2 * align256((size_t)nnz * 4) + align256((size_t)nnz * 8) +
+           align256((size_t)p.ntiles * 4 << p.dbits) + align256((size_t)4 << p.dbits);
 }
 
 int csr_transpose(int32_t n_rows, int32_t n_cols, int32_t nnz, const int32_t *indptr, IdxRef indices,
@@ -350,67 +383,60 @@ int csr_transpose(int32_t n_rows, int32_t n_cols, int32_t nnz, const int32_t *in
         GCN_LAUNCH_CHECK("fill_zero_kernel");
         return GCN_OK;
     }
-    const int32_t ntiles = (int32_t)(((int64_t)nnz + kTile - 1) / kTile);
+    const SortPlan p = sort_plan(n_cols, nnz);
     Arena ar(ws, ws_bytes);
     uint32_t *ka = ar.take<uint32_t>(nnz), *kb = ar.take<uint32_t>(nnz);
-    int32_t *va = ar.take<int32_t>(nnz), *vb = ar.take<int32_t>(nnz);
-    int32_t *hist = ar.take<int32_t>((size_t)ntiles * kRadix);
-    int32_t *offs = ar.take<int32_t>((size_t)ntiles * kRadix);
-    const int64_t scan_len = (int64_t)ntiles * kRadix;
-    const int64_t segs = (scan_len + kScanSeg - 1) / kScanSeg;
-    int32_t *seg_sums = ar.take<int32_t>((size_t)segs + 1);
-    int32_t *seg_offs = ar.take<int32_t>((size_t)segs + 1);
-    if (!ka || !kb || !va || !vb || !hist || !offs || !seg_sums || !seg_offs) {
+    uint2 *pairs = ar.take<uint2>(nnz);
+    int32_t *hist = ar.take<int32_t>((size_t)p.ntiles << p.dbits);
+    int32_t *total = ar.take<int32_t>((size_t)1 << p.dbits);
+    if (!ka || !kb || !pairs || !hist || !total) {
         set_error("csr_transpose: workspace too small (%zu < %zu bytes)", ws_bytes,
                   transpose_workspace_bytes(n_rows, n_cols, nnz));
         return GCN_EWORKSPACE;
     }
-    unsigned g = (unsigned)((nnz + kTB - 1) / kTB);
-    if (g > 16384) g = 16384;
+    int32_t *rowid = (int32_t *)kb;   // read by the first pass, before kb is written
     {
-        ProfScope ps(K_T_COUNT, s, 0.0, (double)nnz * 12.0);
-        hipLaunchKernelGGL(iota_kernel, dim3(g), dim3(kTB), 0, s, nnz, indices, ka, va);
-        GCN_LAUNCH_CHECK("iota_kernel");
+        ProfScope ps(K_T_COUNT, s, 0.0, (double)nnz * 4.0);
+        hipLaunchKernelGGL(rowid_kernel, dim3((unsigned)((n_rows + kTB / 64 - 1) / (kTB / 64))), dim3(kTB), 0, s,
+                           n_rows, indptr, rowid);
+        GCN_LAUNCH_CHECK("rowid_kernel");
     }
-    const int bits = key_bits(n_cols);
-    for (int shift = 0; shift < bits || shift == 0; shift += 8) {
+    const uint32_t *kin = nullptr;
+    uint32_t *kout = ka;
+    const int32_t *rows = rowid;
+    const uint32_t mask = (1u << p.dbits) - 1u;
+    for (int pass = 0; pass < p.passes; ++pass) {
+        const int shift = pass * p.dbits;
         {
             ProfScope ps(K_T_COUNT, s, 0.0, (double)nnz * 4.0);
-            hipLaunchKernelGGL(hist_kernel, dim3(ntiles), dim3(kTB), 0, s, nnz, ka, shift, ntiles, hist);
+            hipLaunchKernelGGL(hist_kernel, dim3(p.ntiles), dim3(kTB), 0, s, nnz, indices, kin, shift, mask, p.ntiles,
+                               hist);
             GCN_LAUNCH_CHECK("hist_kernel");
         }
         {
-            ProfScope ps(K_T_SCAN, s, 0.0, (double)scan_len * 8.0);
-            hipLaunchKernelGGL(scan_reduce_kernel, dim3((unsigned)segs), dim3(kTB), 0, s, scan_len, hist,
-                               seg_sums);
-            hipLaunchKernelGGL(scan_small_kernel, dim3(1), dim3(1024), 0, s, segs, seg_sums, seg_offs);
-            hipLaunchKernelGGL(scan_down_kernel, dim3((unsigned)segs), dim3(kTB), 0, s, scan_len, hist, seg_offs,
-                               offs);
-            GCN_LAUNCH_CHECK("scan kernels");
+            ProfScope ps(K_T_SCAN, s, 0.0, (double)p.ntiles * (mask + 1) * 8.0);
+            hipLaunchKernelGGL(scan_tiles_kernel, dim3(mask + 1), dim3(kTB), 0, s, p.ntiles, hist, total);
+            GCN_LAUNCH_CHECK("scan_tiles_kernel");
         }
         {
-            ProfScope ps(K_T_FILL, s, 0.0, (double)nnz * 16.0);
-            hipLaunchKernelGGL(scatter_kernel, dim3(ntiles), dim3(kTB), 0, s, nnz, ka, va, shift, ntiles, offs,
-                               kb, vb);
+            ProfScope ps(K_T_FILL, s, 0.0, (double)nnz * 24.0);
+            // pairs are left by every other pass, counted from the last
+            const bool to_pairs = (p.passes - pass) % 2 == 0;
+            auto kernel = !to_pairs && pass > 0 ? scatter_kernel<true> : scatter_kernel<false>;
+            hipLaunchKernelGGL(kernel, dim3(p.ntiles), dim3(kTB), 0, s, nnz, indices, kin, rows, vals, pairs, shift,
+                               p.dbits, p.ntiles, hist, total, kout, to_pairs ? pairs : nullptr, t_indices, t_vals);
             GCN_LAUNCH_CHECK("scatter_kernel");
         }
-        std::swap(ka, kb);
-        std::swap(va, vb);
+        kin = kout;
+        kout = kout == ka ? kb : ka;
+        rows = t_indices;
+        vals = t_vals;
     }
     {
         ProfScope ps(K_T_FINAL, s, 0.0, (double)(n_cols + 1) * 4.0);
         hipLaunchKernelGGL(bounds_kernel, dim3((unsigned)((n_cols + 1 + kTB - 1) / kTB)), dim3(kTB), 0, s,
-                           n_cols, nnz, ka, t_indptr);
+                           n_cols, nnz, kin, t_indptr);
         GCN_LAUNCH_CHECK("bounds_kernel");
-    }
-    {
-        // the spare key buffer holds the row of every entry
-        int32_t *rowid = (int32_t *)kb;
-        ProfScope ps(K_T_FINAL, s, 0.0, (double)nnz * 20.0);
-        hipLaunchKernelGGL(rowid_kernel, dim3((unsigned)((n_rows + kTB / 64 - 1) / (kTB / 64))), dim3(kTB), 0, s,
-                           n_rows, indptr, rowid);
-        hipLaunchKernelGGL(finalize_kernel, dim3(g), dim3(kTB), 0, s, nnz, rowid, vals, va, t_indices, t_vals);
-        GCN_LAUNCH_CHECK("finalize_kernel");
     }
     return GCN_OK;
 }
