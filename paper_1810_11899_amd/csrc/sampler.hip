@@ -147,7 +147,7 @@ __device__ void dashboard_cleanup(uint16_t *db, Slots sl, int32_t cap, int32_t &
     __syncthreads();
 }
 
-template <bool AHEAD>
+template <bool CAPPED>
 __global__ __launch_bounds__(kSampThreads) void frontier_kernel(SampArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     Slots sl;
@@ -222,12 +222,17 @@ __global__ __launch_bounds__(kSampThreads) void frontier_kernel(SampArgs a) {
     // A step is two dependent loads (the neighbour, then its row bounds), and
     // the next step's pop needs the second one's result: how many entries the
     // new vertex adds.  With a cap that number is nearly always the cap (the
-    // walk prefers vertices of high degree), so with AHEAD two more steps are
+    // walk prefers vertices of high degree), so with a cap two more steps are
     // popped on that guess: iteration i issues the neighbour load of step
     // i + 2 and the row-bound loads of step i + 1, and appends step i, whose
     // loads have had an iteration each.  An append of fewer entries takes the
     // pops behind it back (their vertices are live again) and they are drawn
     // anew from the same random words, so the run is the sequential one.
+    // Where more than about a quarter of the guesses are wrong (degrees mostly
+    // below the cap) a step ahead costs more than it hides, and the rest of
+    // the run goes one step at a time: 256 runs, m = 300, n = 2500, on 100,000
+    // vertices, with pops ahead throughout / one at a time: all guesses right
+    // 1.86 / 2.60 ms, nearly none 4.38 / 2.46, about a third wrong 2.58 / 2.34.
     // The loads of the steady path are issued in every iteration, needed or
     // not, and the paths that fill it wait for theirs: each use then waits for
     // its own load and not for the later ones.
@@ -252,13 +257,13 @@ __global__ __launch_bounds__(kSampThreads) void frontier_kernel(SampArgs a) {
     // Probing rounds until one hits: the lowest of the 64 processors on a live
     // entry wins.  It is nearly always among the first 16, so only their words
     // are drawn, for 16 rounds at once (lane l: processor l % 16, Philox block
-    // pblk + l / 16); a round they all miss is drawn for the other 48.  Without
-    // a cap a popped hub leaves thousands of dead entries and most rounds miss,
-    // so all 64 words are drawn, four rounds at once (30 roots, 2000 vertices
-    // of 20,000, 256 runs: 16 words 7.3 ms, 64 words 3.6 ms; 300 roots,
-    // 2500 vertices, cap 30: 64 words 2.54 ms, 16 words 2.55 ms with the pops
-    // ahead, which the larger graphs gain from).
-    auto probe = [&](int32_t in_use, uint64_t &rnd, int32_t limit) __attribute__((always_inline)) -> int32_t {
+    // pblk + l / 16); a round they all miss is drawn for the other 48.  One
+    // step at a time (without a cap a popped hub leaves thousands of dead
+    // entries, and most rounds miss) all 64 words are drawn, four rounds at
+    // once: 30 roots, 2000 vertices of 20,000, no cap, 256 runs: 16 words
+    // first 7.3 ms, 64 words 3.6 ms.
+    auto probe = [&](auto mode, int32_t in_use, uint64_t &rnd, int32_t limit) __attribute__((always_inline)) -> int32_t {
+        constexpr bool AHEAD = decltype(mode)::value;
         for (int32_t rr = 0; rr < limit; ++rr) {
             const uint64_t blk = rnd >> 2;
             if (!AHEAD) {
@@ -339,13 +344,15 @@ __global__ __launch_bounds__(kSampThreads) void frontier_kernel(SampArgs a) {
         prov = ps + 1;
         lds_order();
         uint64_t rnd = prev.round;
-        const int32_t k = probe(used + j * a.cap, rnd, 8);
+        const int32_t k = probe(std::true_type{}, used + j * a.cap, rnd, 8);
         if (k < 0 || k >= s) return 0;              // none, or a vertex that is not known yet
         x.round = rnd;
         popped = j + 1;
         return take(x, k, i - a.m + j);
     };
-    auto step = [&](auto phase) __attribute__((always_inline)) -> bool {
+    int32_t wrong = 0;        // guesses taken back
+    auto step = [&](auto mode, auto phase) __attribute__((always_inline)) -> bool {
+        constexpr bool AHEAD = decltype(mode)::value;   // pops ahead, or one step at a time
         constexpr int P = decltype(phase)::value;
         Step &c = q[P], &n1 = q[(P + 1) % 3], &n2 = q[(P + 2) % 3];
         // (the same in every lane; said here so that the step's branches and
@@ -369,7 +376,7 @@ __global__ __launch_bounds__(kSampThreads) void frontier_kernel(SampArgs a) {
         if (popped < (AHEAD ? 2 : 1)) {
             if (popped == 0) {
                 c.round = round;
-                const int32_t k = probe(used, c.round, (int32_t)kProbeRoundLimit);
+                const int32_t k = probe(mode, used, c.round, (int32_t)kProbeRoundLimit);
                 if (k < 0) { status = GCN_SAMPLE_PROBE_LIMIT; return false; }
                 c.v = load1(a.indices, take(c, k, i - a.m));
                 popped = 1;
@@ -415,6 +422,7 @@ __global__ __launch_bounds__(kSampThreads) void frontier_kernel(SampArgs a) {
             }
             popped = 0;
             prov = s;
+            wrong = uniform(wrong) + 1;
         }
         lds_order();
         if (i - flushed == 64) {
@@ -423,9 +431,26 @@ __global__ __launch_bounds__(kSampThreads) void frontier_kernel(SampArgs a) {
         }
         return i < a.n;
     };
-    if (status == GCN_SAMPLE_OK && i < a.n)
-        while (step(std::integral_constant<int, 0>{}) && step(std::integral_constant<int, 1>{}) &&
-               step(std::integral_constant<int, 2>{})) {
+    bool more = status == GCN_SAMPLE_OK && i < a.n;
+    if (CAPPED && more) {
+        const std::true_type ahead_mode{};
+        while ((more = step(ahead_mode, std::integral_constant<int, 0>{}) &&
+                       step(ahead_mode, std::integral_constant<int, 1>{}) &&
+                       step(ahead_mode, std::integral_constant<int, 2>{})) &&
+               wrong <= 16 + ((i - a.m) >> 2)) {
+        }
+        if (more) {   // the pops ahead are taken back
+            if (lane == 0) {
+                if (popped > 0) sl.bd[q[0].k].y |= (int32_t)kLive;
+                if (popped > 1) sl.bd[q[1].k].y |= (int32_t)kLive;
+            }
+            lds_order();
+            popped = 0;
+            pblk = ~0ull - 8;
+        }
+    }
+    if (more)
+        while (step(std::false_type{}, std::integral_constant<int, 0>{})) {
         }
     if (flushed + ((lane - flushed) & 63) < i) out[flushed + ((lane - flushed) & 63)] = held;
     if (lane == 0) {
@@ -809,8 +834,11 @@ int frontier_sample(const SampArgs &a, int32_t S, size_t lds, hipStream_t s) {
         hipFuncSetAttribute((const void *)frontier_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             kSamplerMaxLds);
     });
-    // without a cap a vertex's entries are its degree, which cannot be guessed
-    if (a.cap > 0) frontier_kernel<true><<<S, kSampThreads, lds, s>>>(a);
+    // without a cap, or with one that few degrees reach, a vertex's entries are
+    // its degree, which cannot be guessed, and a Dashboard may have no room for
+    // the guess (cap 5000: 4.56 ms with pops ahead, 1.73 without; cap 128 on
+    // 200,000 vertices of degree 40: 2.85 and 2.75; cap 64: 2.41 and 2.65)
+    if (a.cap > 0 && a.cap <= 256) frontier_kernel<true><<<S, kSampThreads, lds, s>>>(a);
     else frontier_kernel<false><<<S, kSampThreads, lds, s>>>(a);
     GCN_LAUNCH_CHECK("frontier_kernel");
     return GCN_OK;

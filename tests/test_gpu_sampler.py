@@ -271,3 +271,14 @@ def test_frontier_pops_ahead_match_oracle(cap, m, n):
     wmax = int(np.minimum(g.degrees(), cap).max())
     run_and_compare(g, params_for(g, m, n, cap=cap, seed=3), 4)
     run_and_compare(g, params_for(g, m, n, cap=cap, seed=4, db=m * wmax + cap, ia=m + 3), 4, first=2)
+
+
+@pytest.mark.parametrize("cap, d", [(4, 8), (8, 8), (12, 8), (30, 8), (200, 8)])
+def test_frontier_gives_up_pops_ahead(cap, d):
+    """Degrees around and below the cap: the pops ahead are nearly never,
+    sometimes and nearly always taken back, and a run that gives them up goes
+    on one step at a time with the same random words."""
+    g = synth.custom(3000, "er", d, [(4, 4)], seed=cap).graph
+    run_and_compare(g, params_for(g, 50, 700, cap=cap, seed=11), 6)
+    wmax = int(np.minimum(g.degrees(), cap).max())
+    run_and_compare(g, params_for(g, 40, 500, cap=cap, seed=12, db=40 * wmax + cap, ia=45), 4, first=1)
