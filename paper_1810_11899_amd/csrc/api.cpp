@@ -162,28 +162,33 @@ struct LayerPlan {
 // copy of those operands is made.  Otherwise (shapes the large-tile kernel
 // does not take) the products run NT on transposed copies.
 //
-// A layer that converts its input itself keeps the rows (and AGG's) with zero
-// columns up to a multiple of 8; `packed`: the input rows come from the layer
-// below with leading dimension f_in.
+// Such a layer keeps its input rows (and AGG's) with zero columns up to a
+// multiple of 8.  The rows' layout depends on the sizes alone, not on who
+// wrote them, so that a saved buffer of a model step and one of a layer call
+// are read alike.
 int32_t pad8(int32_t f) { return (f + 7) & ~7; }
-bool bf16_dw_rowmajor(int32_t n, int32_t f_in, int32_t h, bool packed) {
+bool bf16_dw_rowmajor(int32_t n, int32_t f_in, int32_t h) {
     if (n <= 0) return false;
     const void *p = (const void *)(uintptr_t)256;   // stands for 256-byte aligned buffers
     GemmProblem g[2] = {};
     for (int i = 0; i < 2; ++i) {
         g[i].M = f_in;
         g[i].N = h;
-        g[i].seg[0] = GemmSeg{p, packed ? f_in : pad8(f_in), p, 2 * (int64_t)h, n};
+        g[i].seg[0] = GemmSeg{p, pad8(f_in), p, 2 * (int64_t)h, n};
     }
     return gemm_bf16_big_ok(L_TN, 2, g) && h % 8 == 0;
 }
 
-// leading dimension of a bfloat16 layer's input rows H16 and AGG16
-int32_t bf16_ld(int32_t n, int32_t f_in, int32_t h, bool packed) {
-    return !packed && bf16_dw_rowmajor(n, f_in, h, false) ? pad8(f_in) : f_in;
-}
+// leading dimension of the input rows and AGG rows a bfloat16 layer multiplies
+int32_t bf16_ld(int32_t n, int32_t f_in, int32_t h) { return bf16_dw_rowmajor(n, f_in, h) ? pad8(f_in) : f_in; }
 // one of the four copies in a bfloat16 layer's saved buffer
 size_t saved_one(int32_t n, int32_t f_in) { return align256((size_t)n * pad8(f_in) * 2); }
+// the input rows in a saved buffer: the first copy, or, where they are padded,
+// the second (in the place of the transposed rows, which such a layer does not
+// read): a layer below writes its output unpadded to the first
+size_t saved_rows_at(int32_t n, int32_t f_in, int32_t h) {
+    return bf16_ld(n, f_in, h) == f_in ? 0 : saved_one(n, f_in);
+}
 
 int32_t pad_classes(int32_t C);
 
@@ -305,8 +310,9 @@ LayerPlan plan_layer(int32_t n, int32_t nnz, int32_t f_in, int32_t h, int order,
     return p;
 }
 
-// float32: AGG (aggregate-first only).  bfloat16: H16, H16^T, then AGG16 and
-// AGG16^T (aggregate-first), each n x f_in (rows of up to pad8(f_in)).
+// float32: AGG (aggregate-first only).  bfloat16: H16, H16^T (or padded H16,
+// saved_rows_at), then AGG16 and AGG16^T (aggregate-first), each n x f_in (rows
+// of up to pad8(f_in)).
 size_t saved_bytes(int32_t n, int32_t f_in, int32_t h, int order, int prec) {
     (void)h;
     if (prec == GCN_BF16) {
@@ -466,7 +472,7 @@ size_t gcn_layer_workspace_bytes(int32_t n, int32_t nnz, int32_t f_in, int32_t h
 // the next consumer multiplies with (the next layer's input copies in its
 // saved buffer, or the head's), and that consumer skips its conversion.
 struct Bf16Link {
-    bool in_ready = false;        // saved already holds this layer's H16 and H16^T
+    bool in_ready = false;        // saved already holds this layer's H16 (n x f_in) and, where read, H16^T
     uint16_t *out16 = nullptr;    // bf16(Y) rows, n x 2h (leading dim 2h)
     uint16_t *out16T = nullptr;   // bf16(Y)^T, 2h x n (leading dim n)
     const uint16_t *WsT = nullptr, *WnT = nullptr;   // bf16(W_self)^T, bf16(W_neigh)^T, already made
@@ -503,7 +509,7 @@ static int layer_fwd(bool launch, const gcn_csr *A, const float *H, int32_t f_in
         // bfloat16 operands, every product in NT form (both operands contiguous
         // along K); saved = H16 | H16^T | AGG16 | AGG16^T
         const size_t one = saved_one(n, f_in);
-        uint16_t *H16 = (uint16_t *)saved;
+        uint16_t *H16 = (uint16_t *)((char *)saved + saved_rows_at(n, f_in, h));
         uint16_t *H16T = (uint16_t *)((char *)saved + one);
         uint16_t *AGG16 = af ? (uint16_t *)((char *)saved + 2 * one) : nullptr;
         uint16_t *AGG16T = af ? (uint16_t *)((char *)saved + 3 * one) : nullptr;
@@ -511,12 +517,14 @@ static int layer_fwd(bool launch, const gcn_csr *A, const float *H, int32_t f_in
         uint16_t *WnT = lk.WsT ? const_cast<uint16_t *>(lk.WnT) : ar.take<uint16_t>((size_t)pad8(f_in) * h);
         // H16 (and H16T for the transposed weight-gradient products) in one
         // pass over H, unless the layer below wrote them
-        const bool tnw = bf16_dw_rowmajor(n, f_in, h, lk.in_ready);
-        const int32_t fp = bf16_ld(n, f_in, h, lk.in_ready);   // the rows of H16, AGG16, W^T
+        const bool tnw = bf16_dw_rowmajor(n, f_in, h);
+        const int32_t fp = bf16_ld(n, f_in, h);   // the rows of H16, AGG16, W^T
         if (!lk.in_ready) {
             rc = tnw ? cvt_bf16_pad(n, f_in, H, ldh, H16, fp, fp, s)
                      : transpose_bf16_copy(n, f_in, H, 0, ldh, H16T, n, H16, f_in, s);
             if (rc) return rc;
+        } else if (fp != f_in && (rc = pad_rows_bf16(n, f_in, (const uint16_t *)saved, H16, fp, s))) {
+            return rc;
         }
         if (!lk.WsT) {
             Bf16PrepBatch wb;
@@ -616,8 +624,7 @@ static int layer_bwd(bool launch, const gcn_csr *A, const gcn_csr *AT, const flo
                      void *ws, size_t ws_bytes, void *stream, bool dz_ready = false,
                      float *below_dbias = nullptr, const int32_t *bAT = nullptr, bool dzT_ready = false,
                      int32_t below_tcols = 0, const uint16_t *Ws16_ready = nullptr,
-                     const uint16_t *Wn16_ready = nullptr, bool packed = false) {
-    // packed (bfloat16): the saved input rows came from the layer below
+                     const uint16_t *Wn16_ready = nullptr) {
     // bAT: A^T's merge-path row ranges (spmm_bounds), or NULL
     // dzT_ready (bfloat16, with dz_ready): the producer of dY also wrote
     // dZ^T (2h x n, leading dim n) behind the packed dZ rows in the same
@@ -708,12 +715,12 @@ static int layer_bwd(bool launch, const gcn_csr *A, const gcn_csr *AT, const flo
     // a7: weight gradients, K = n, split-K
     GemmProblem g[2] = {dw_problem(f_in, h, n), dw_problem(f_in, h, n)};
     int layout = L_TN;
-    if (bf && bf16_dw_rowmajor(n, f_in, h, packed)) {
+    if (bf && bf16_dw_rowmajor(n, f_in, h)) {
         // TN form on the row-major operands: dW_self = H^T dZ_s, dW_neigh =
         // AGG^T dZ_n (aggregate-first) or H^T G (transform-first)
         const size_t one = saved_one(n, f_in);
-        const int32_t fp = bf16_ld(n, f_in, h, packed);
-        const uint16_t *H16 = (const uint16_t *)saved;
+        const int32_t fp = bf16_ld(n, f_in, h);
+        const uint16_t *H16 = (const uint16_t *)((const char *)saved + saved_rows_at(n, f_in, h));
         layout = L_TN;
         g[0].seg[0] = GemmSeg{H16, fp, Zs, ldZs, n};
         if (!af) g[1].seg[0] = GemmSeg{H16, fp, Gp, ldG, n};
@@ -1098,7 +1105,7 @@ static size_t model_w16_bytes(int32_t n, int32_t L, const gcn_layer_args *layers
     for (int32_t l = 0; l < L; ++l) {
         const gcn_layer_args &a = layers[l];
         const size_t one = (size_t)a.f_in * a.h * 2;
-        const int32_t fp = bf16_ld(n, a.f_in, a.h, l > 0);
+        const int32_t fp = bf16_ld(n, a.f_in, a.h);
         uint16_t *st = carve((size_t)fp * a.h * 2), *nt = carve((size_t)fp * a.h * 2);
         if (batch) {
             batch->add(a.W_self, a.h, a.f_in, a.h, st, fp, fp, true);
@@ -1206,7 +1213,7 @@ int model_step(bool launch, const gcn_csr *A, const gcn_csr *AT, const float *H0
             if (l + 1 < L) {
                 const gcn_layer_args &nx = layers[l + 1];
                 lk.out16 = (uint16_t *)nx.saved;
-                if (!bf16_dw_rowmajor(n, nx.f_in, nx.h, true))   // only the transposed products read H16T
+                if (!bf16_dw_rowmajor(n, nx.f_in, nx.h))   // only the transposed products read H16T
                     lk.out16T = (uint16_t *)((char *)nx.saved + saved_one(n, nx.f_in));
             } else if (head) {
                 lk.out16 = HL16;
@@ -1225,7 +1232,7 @@ int model_step(bool launch, const gcn_csr *A, const gcn_csr *AT, const float *H0
     // aggregate-first (dW_self and dW_neigh), the self half for
     // transform-first (dW_neigh takes A^T dZ_n, transposed after the SpMM)
     auto tcols = [&](int32_t l) {
-        if (!bf || bf16_dw_rowmajor(n, layers[l].f_in, layers[l].h, l > 0)) return 0;
+        if (!bf || bf16_dw_rowmajor(n, layers[l].f_in, layers[l].h)) return 0;
         return layers[l].order == GCN_AGGREGATE_FIRST ? 2 * layers[l].h : layers[l].h;
     };
     const float *g = dY;  // PREDICT + LOSS, or the given output gradient
@@ -1254,7 +1261,7 @@ int model_step(bool launch, const gcn_csr *A, const gcn_csr *AT, const float *H0
         if ((rc = layer_bwd(launch, A, AT, Hin, a.f_in, ldin, a.W_self, a.W_neigh, a.h, a.Y, a.ldy, a.saved,
                             a.saved_bytes, g, ldg, a.dH, a.lddh, a.dW_self, a.dW_neigh, a.dbias, a.order, prec, ws,
                             ws_bytes, stream, ready, fuse ? layers[l - 1].dbias : nullptr, bAT,
-                            ready && tcols(l) > 0, fuse ? tcols(l - 1) : 0, w16.Ws16[l], w16.Wn16[l], l > 0)))
+                            ready && tcols(l) > 0, fuse ? tcols(l - 1) : 0, w16.Ws16[l], w16.Wn16[l])))
             return rc;
         g = a.dH;
         ldg = a.lddh;

@@ -292,6 +292,8 @@ int cvt_bf16(int64_t rows, int64_t cols, const float *x, int64_t ldx, uint16_t *
 // the same, and columns cols .. ycols-1 of y set to zero (K padding)
 int cvt_bf16_pad(int64_t rows, int64_t cols, const float *x, int64_t ldx, uint16_t *y, int64_t ldy,
                  int64_t ycols, hipStream_t s);
+// y (rows x ldy) = x (rows x cols, packed; both bfloat16, even widths), zeros past cols
+int pad_rows_bf16(int64_t rows, int32_t cols, const uint16_t *x, uint16_t *y, int32_t ldy, hipStream_t s);
 
 // CSR transpose --------------------------------------------------------------
 // values of A^T for a symmetric pattern (A^T shares A's indptr / indices)

@@ -779,6 +779,34 @@ int cvt_bf16_pad(int64_t rows, int64_t cols, const float *x, int64_t ldx, uint16
     return GCN_OK;
 }
 
+// y (rows x ldy) = x (rows x cols, packed), both bfloat16, zero columns past
+// cols.  A word is two columns: cols and ldy are even (cols is a layer's 2h).
+// Only layers behind one whose 2h is not a multiple of 8 need it.
+namespace {
+__global__ __launch_bounds__(256) void pad_rows_bf16_kernel(int64_t rows, int32_t cw, int32_t yw,
+                                                            const uint32_t *__restrict__ x, uint32_t *__restrict__ y) {
+    const int64_t n = rows * yw, stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+        const int64_t r = i / yw;
+        const int32_t c = (int32_t)(i - r * yw);
+        y[i] = c < cw ? x[r * cw + c] : 0u;
+    }
+}
+}  // namespace
+int pad_rows_bf16(int64_t rows, int32_t cols, const uint16_t *x, uint16_t *y, int32_t ldy, hipStream_t s) {
+    if (rows <= 0) return GCN_OK;
+    if (cols % 2 || ldy % 2 || ldy < cols) {
+        set_error("pad_rows_bf16: %d columns into rows of %d", cols, ldy);
+        return GCN_EINVAL;
+    }
+    const int64_t blocks = std::min<int64_t>(8192, (rows * (ldy / 2) + 255) / 256);
+    ProfScope ps(K_CVT_BF16, s, 0.0, (double)rows * (cols + ldy) * 2.0);
+    hipLaunchKernelGGL(pad_rows_bf16_kernel, dim3((unsigned)blocks), dim3(256), 0, s, rows, cols / 2, ldy / 2,
+                       (const uint32_t *)x, (uint32_t *)y);
+    GCN_LAUNCH_CHECK("pad_rows_bf16_kernel");
+    return GCN_OK;
+}
+
 // Several small float32 matrices (a step's weights) to bfloat16 in one
 // launch: each job is a plain copy (columns cols .. dcols-1 of a row zero)
 // or a transposed one (dst, cols x rows, = bf16(src)^T), in 32 x 32 tiles,
