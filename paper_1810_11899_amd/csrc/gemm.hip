@@ -124,13 +124,18 @@ __device__ __forceinline__ bool decode_block(const DevArgs &a, BlockCoord &c) {
 // i.e. 1.2 PFLOP/s of bfloat16 work: the clock falls to 1.9 GHz under it
 // (2.4 on zero operands), with the matrix cores busy 62% of the cycles.
 //
-// Range: an infinity or a float32 above the largest bfloat16 has no split,
-// parts of an element below about 2^-109 fall under the bfloat16 subnormals,
-// and sums that overflow could meet opposite infinities part by part.
-// Each of these shows in a block's sums: a block that holds a sum that is not
-// finite, or one that is not zero and below 2^-90, is computed again on the
-// float32 cores before the epilogue, so infinities, NaN, overflow and tiny
-// operands give what float32 products give.
+// Range: unscaled, the parts of an element below 2^-109 fall under the
+// smallest bfloat16, and nothing in the sums tells it (such an element times a
+// large one is an ordinary number).  So elements are multiplied by 2^24 as
+// they are split and the sums by 2^-48 at the end: every part of every float32
+// from the smallest subnormal up is then a normal bfloat16, and results down
+// to the smallest subnormal keep their bits.  That leaves elements from 2^103
+// on, infinities and NaN, and sums past 2^79: a part or a partial sum of these
+// is an infinity or NaN, and so is every sum it goes into.  A block that holds
+// a sum that is not finite is computed again, unscaled, on the float32 cores
+// before the epilogue and gives what float32 products give.  (So an element of
+// a block can take either path, and differ in its last bits, by what another
+// row of the block holds; the block costs the second pass too.)
 //
 // LDS: per operand and k-tile of 16, three planes (h, m, l) of two chunks
 // (k 0-7, k 8-15) of XT rows x 16 bytes, so that a fragment read (8
@@ -145,8 +150,11 @@ typedef float float4a4 __attribute__((ext_vector_type(4), aligned(4)));   // 16-
 constexpr int kBK = 16;           // K depth of one LDS stage
 constexpr int64_t kFastLd = 1 << 22;   // leading dimensions whose tile offsets fit 32 bits
 
-// x0, x1 -> the packed h, m and l parts
+constexpr float kSplitScale = 0x1p24f, kSumScale = 0x1p-48f;
+// x0, x1 -> the packed h, m and l parts of kSplitScale times them
 __device__ __forceinline__ void split3(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l) {
+    x0 *= kSplitScale;
+    x1 *= kSplitScale;
     h = pack_bf16x2(x0, x1);
     const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xFFFF0000u);
     m = pack_bf16x2(r0, r1);
@@ -380,19 +388,17 @@ void gemm_kernel(DevArgs args) {
     }
     // ---- sums outside the split's range: the block again on the float32 cores
     {
-        uint32_t hi = 0u, lo = 0xFFFFFFFFu;
+        uint32_t hi = 0u;
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int j = 0; j < FN; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const uint32_t u = __float_as_uint(acc[i][j][r]) & 0x7FFFFFFFu;
-                    hi = max(hi, u);
-                    lo = min(lo, u - 1u);   // (a zero becomes the largest)
+                    hi = max(hi, __float_as_uint(acc[i][j][r]) & 0x7FFFFFFFu);
+                    acc[i][j][r] *= kSumScale;
                 }
-        constexpr uint32_t kInf = 0x7F800000u, kTiny = (127u - 90u) << 23;
-        if (__syncthreads_or(hi >= kInf || lo < kTiny - 1u)) {
+        if (__syncthreads_or(hi >= 0x7F800000u)) {
             float *As = (float *)smem, *Bs = As + kBK * (TBM + 4);
             static_assert((kBK * (TBM + 4 + TBN + 4)) * 4 <= sizeof(smem), "float32 tiles fit");
             clear();

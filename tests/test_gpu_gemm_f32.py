@@ -46,12 +46,12 @@ def run(H, Ws, dY):
     return out[0], out[1], dWs.cpu().numpy(), dH.cpu().numpy()
 
 
-def check(got, a, b, K):
+def check(got, a, b, K, least=1e-37):
     """|got - a b| within three roundings per 16 k, the split's dropped parts
     and the split-K sums, each at most 2^-24 of sum |a||b|."""
     ref = a.astype(np.float64) @ b.astype(np.float64)
     mag = np.abs(a).astype(np.float64) @ np.abs(b).astype(np.float64)
-    bound = (3.0 * K / 16 + 16 + 64) * 2.0 ** -24 * mag + 1e-37
+    bound = (3.0 * K / 16 + 16 + 64) * 2.0 ** -24 * mag + least
     assert np.all(np.abs(got - ref) <= bound), float((np.abs(got - ref) / (mag + 1e-300)).max())
 
 
@@ -114,3 +114,25 @@ def test_products_outside_the_split_range(n, f, h):
     assert np.all(np.isposinf(dH[0])) and np.all(np.isnan(dH[1]))
     ref = dY[2].astype(np.float64) @ Ws2.T.astype(np.float64)
     assert np.allclose(dH[2], ref, rtol=2e-6, atol=0)
+
+
+@pytest.mark.parametrize("n, f, h", [(200, 48, 40), (66000, 48, 260)])
+@pytest.mark.parametrize("e", [-145, -135, -126, -118, -109, -60, 110])
+def test_products_of_tiny_and_large(e, n, f, h):
+    """Elements of about 2^e times elements of about 2^-e: ordinary sums of
+    operands from the smallest subnormals up, to float32's own accuracy; and
+    tiny elements beside ordinary ones that meet a zero."""
+    rg = np.random.default_rng(n - e)
+    tiny = lambda s: np.ldexp(rg.standard_normal(s), e).astype(np.float32)                       # noqa: E731
+    large = lambda s: np.ldexp(rg.standard_normal(s), min(-e, 118) - 20).astype(np.float32)      # noqa: E731
+    H, Ws = tiny((n, f)), large((f, h))
+    H[::3, 5] = 1.0          # (the product's column 5 of H meets zeros)
+    Ws[5] = 0.0
+    dY = large((n, h))
+    pos, neg, dW, _ = run(H, Ws, dY)
+    check(pos - neg, H, Ws, f, 1e-43)
+    rest = np.arange(f) != 5
+    check(dW[rest], H[:, rest].T, dY, n, 1e-43)
+    dY = tiny((n, h))
+    _, _, dW, dH = run(large((n, f)), Ws, dY)
+    check(dH, dY, Ws.T, h, 1e-43)
