@@ -116,6 +116,13 @@ __device__ __forceinline__ bool decode_block(const DevArgs &a, BlockCoord &c) {
 // zero.  (All six on the accumulator are 10% faster but up to 1.7 times the
 // float32 cores' error there; h h' last on the small sum leaves a bias that
 // adds up over split-K partials.)
+// Short sums have no such roundings to save, and there the parts left out
+// show: K = 1 2.6e-8 / 2.5e-8, its largest error 0.88 / 0.60e-7 of |x x'|,
+// that of K = 2 1.58 / 1.13e-7 of sum |x x'| (K = 3 1.27 / 1.47e-7).  Products
+// of K <= 2 therefore run on the float32 cores.  The same holds for a row of a
+// long product in which few elements are not zero, where a k-tile's one term
+// is rounded twice: 1 / 2 / 4 / 8 elements of 602 2.6e-8 / 2.5e-8, 3.9 / 3.5,
+// 4.9 / 4.4, 5.9 / 5.1.
 //
 // Why: the bfloat16 cores do 16 times the float32 cores' rate, so six
 // products leave 2.7 times the float32 peak.  Measured at 65,536 vertices
@@ -329,14 +336,16 @@ void gemm_kernel(DevArgs args) {
                 for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
     };
     clear();
-    if (kt_begin < kt_end) {
+    const bool f32_cores = K0 + K1 <= 2;   // (see above; one or two k-tiles)
+    const int kt_split = f32_cores ? kt_begin : kt_end;
+    if (kt_begin < kt_split) {
         load(kt_begin);
         la.store(smem);
         lb.store(smem + LA::kElems);
         if (kt_begin + 1 < kt_end) load(kt_begin + 1);
     }
     int buf = 0;
-    for (int kt = kt_begin; kt < kt_end; ++kt) {
+    for (int kt = kt_begin; kt < kt_split; ++kt) {
         __syncthreads();   // this stage is stored, and the other one is read
         const uint16_t *As = smem + buf * kBuf, *Bs = As + LA::kElems;
         bf16x8 b[3][FN], a[3];
@@ -386,7 +395,7 @@ void gemm_kernel(DevArgs args) {
         }
         buf ^= 1;
     }
-    // ---- sums outside the split's range: the block again on the float32 cores
+    // ---- sums outside the split's range, and the shortest: on the float32 cores
     {
         uint32_t hi = 0u;
 #pragma unroll
@@ -398,7 +407,7 @@ void gemm_kernel(DevArgs args) {
                     hi = max(hi, __float_as_uint(acc[i][j][r]) & 0x7FFFFFFFu);
                     acc[i][j][r] *= kSumScale;
                 }
-        if (__syncthreads_or(hi >= 0x7F800000u)) {
+        if (__syncthreads_or(f32_cores || hi >= 0x7F800000u)) {
             float *As = (float *)smem, *Bs = As + kBK * (TBM + 4);
             static_assert((kBK * (TBM + 4 + TBN + 4)) * 4 <= sizeof(smem), "float32 tiles fit");
             clear();

@@ -136,3 +136,26 @@ def test_products_of_tiny_and_large(e, n, f, h):
     dY = tiny((n, h))
     _, _, dW, dH = run(large((n, f)), Ws, dY)
     check(dH, dY, Ws.T, h, 1e-43)
+
+
+@pytest.mark.parametrize("K", [1, 2])
+def test_shortest_sums(K):
+    """One term is the rounded product; two are within two roundings of the
+    larger magnitude (2 x 2^-24 of sum |a||b|)."""
+    rg = np.random.default_rng(K)
+    A, Bm = (rg.standard_normal(s, dtype=np.float32) for s in ((3000, K), (K, 160)))
+
+    def shortest(got, a, b):
+        ref = a.astype(np.float64) @ b.astype(np.float64)
+        if K == 1:
+            assert np.array_equal(got, ref.astype(np.float32))
+        mag = np.abs(a).astype(np.float64) @ np.abs(b).astype(np.float64)
+        assert np.all(np.abs(got - ref) <= 2.0 ** -23 * mag)
+
+    pos, neg, _, _ = run(A, Bm, np.zeros((3000, 160), np.float32))
+    shortest(pos - neg, A, Bm)
+    _, _, dW, _ = run(np.ascontiguousarray(A.T), np.zeros((3000, 160), np.float32), Bm)     # n = K
+    shortest(dW, A, Bm)
+    if K == 1:    # the input gradient: K = 2h = 2, the other half's term zero
+        _, _, _, dH = run(np.ones((3000, 160), np.float32), np.ascontiguousarray(Bm.T), A)
+        shortest(dH, A, Bm)
