@@ -604,23 +604,24 @@ __device__ __forceinline__ void load_row_bounds(int2 *rb, const int32_t *indptr,
 // Calls f(w) for the row's neighbours, 64 at a time in order (lane l of a
 // piece has its l-th neighbour; w = -1 past the row's end), with up to
 // kRowChunks pieces loaded ahead of their use.  Loads past the end are clamped
-// to the row's last neighbour.
+// to the row's last neighbour.  (Unsigned offsets within the row: they pass its
+// end by up to a round of pieces, and rows end at up to 2^31 - 1.)
 template <class F>
 __device__ __forceinline__ void for_row(const int32_t *__restrict__ indices, int2 b, int lane, F f) {
-    int32_t p0 = b.x;
-    for (; b.y - p0 > 64; p0 += 64 * kRowChunks) {
+    const uint32_t len = b.y > b.x ? (uint32_t)b.y - (uint32_t)b.x : 0u, l = (uint32_t)lane;
+    const int32_t *__restrict__ row = indices + b.x;
+    uint32_t o = 0;
+    for (; o + 64 < len; o += 64 * kRowChunks) {
         int32_t w[kRowChunks];
 #pragma unroll
-        for (int c = 0; c < kRowChunks; ++c) w[c] = indices[min(p0 + 64 * c + lane, b.y - 1)];
+        for (int c = 0; c < kRowChunks; ++c) w[c] = row[min(o + 64 * c + l, len - 1)];
 #pragma unroll
-        for (int c = 0; c < kRowChunks; ++c) {
-            const int32_t p = p0 + 64 * c;
-            if (p < b.y) f(p + lane < b.y ? w[c] : -1);
-        }
+        for (int c = 0; c < kRowChunks; ++c)
+            if (o + 64 * c < len) f(o + 64 * c + l < len ? w[c] : -1);
     }
-    if (p0 < b.y) {
-        const int32_t w = indices[min(p0 + lane, b.y - 1)];
-        f(p0 + lane < b.y ? w : -1);
+    if (o < len) {
+        const int32_t w = row[min(o + l, len - 1)];
+        f(o + l < len ? w : -1);
     }
 }
 
