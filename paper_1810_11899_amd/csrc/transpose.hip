@@ -228,7 +228,9 @@ __global__ __launch_bounds__(kTB) void rowid_kernel(int32_t n_rows, const int32_
     const int64_t r = (int64_t)blockIdx.x * (kTB / 64) + (threadIdx.x >> 6);
     if (r >= n_rows) return;
     const int32_t b = indptr[r], e = indptr[r + 1];
-    for (int32_t p = b + (int32_t)(threadIdx.x & 63); p < e; p += 64) rowid[p] = (int32_t)r;
+    // (64-bit positions here and in the other row walks: a lane's last one passes
+    // the row's end, which is at up to 2^31 - 1)
+    for (int64_t p = (int64_t)b + (threadIdx.x & 63); p < e; p += 64) rowid[p] = (int32_t)r;
 }
 
 // Symmetric pattern: A^T has A's row pointers and indices; the value at
@@ -261,7 +263,7 @@ __global__ __launch_bounds__(kTB) void sym_rows_kernel(int32_t n, const int32_t 
         uint32_t v[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int32_t p = b + gl + 16 * u;
+            const int64_t p = (int64_t)b + gl + 16 * u;
             v[u] = p < e ? __float_as_uint(vals[p]) : first;
         }
 #pragma unroll
@@ -278,7 +280,7 @@ __global__ __launch_bounds__(kTB) void sym_rows_kernel(int32_t n, const int32_t 
         const uint32_t lf = __shfl(first, 16 * lg);
         bool s2 = true;
         constexpr int U = 8;
-        int32_t p = lb + lane;
+        int64_t p = (int64_t)lb + lane;
         for (; p + 64 * (U - 1) < le; p += 64 * U) {
             uint32_t v[U];
 #pragma unroll
@@ -499,13 +501,13 @@ __global__ __launch_bounds__(256) void validate_rows_kernel(int32_t n_rows, int3
     if (b < 0 || e > nnz) return;   // then an endpoint or a decrease is reported elsewhere
     // the row's first bad entry: lanes take entries b + lane, b + lane + 64, ...
     int64_t mine = kValidKey;
-    for (int32_t p = b + lane; p < e; p += 64) {
+    for (int64_t p = (int64_t)b + lane; p < e; p += 64) {
         const int32_t j = indices[p];
         int bad = -1;
         if (j < 0 || j >= n_cols) bad = 0;
         else if (sorted && p > b && indices[p - 1] >= j) bad = 1;
         if (bad >= 0) {
-            mine = base | (int64_t)(1 + 2 * (int64_t)(p - b) + bad);
+            mine = base | (1 + 2 * (p - b) + bad);
             break;
         }
     }
