@@ -756,7 +756,11 @@ __global__ __launch_bounds__(kRowThreads) void fill_rows_kernel(int32_t nV, int3
         const float val = ri[i];
         int64_t pos = base + rp[i - r0];   // where the ring's first id goes
         int32_t head = 0, held = 0;        // the ring holds ids head .. head + held - 1
+        // lanes read what others stored: the stores come before, and the next
+        // ones after (a wavefront's LDS accesses execute in order, so the
+        // fences only keep the compiler from moving them)
         auto flush = [&](int32_t cnt) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             if (lane < cnt) {
                 const int32_t loc = ring[(head + lane) & (kRing - 1)];
                 const int64_t q = pos + lane;
@@ -764,7 +768,8 @@ __global__ __launch_bounds__(kRowThreads) void fill_rows_kernel(int32_t nV, int3
                 sub_vals[q] = val;
                 if (sub_vals_t) sub_vals_t[q] = ri[loc];
             }
-            head += cnt;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            head = (head + cnt) & (kRing - 1);
             held -= cnt;
             pos += cnt;
         };
