@@ -228,9 +228,11 @@ __global__ __launch_bounds__(kTB) void rowid_kernel(int32_t n_rows, const int32_
     const int64_t r = (int64_t)blockIdx.x * (kTB / 64) + (threadIdx.x >> 6);
     if (r >= n_rows) return;
     const int32_t b = indptr[r], e = indptr[r + 1];
-    // (64-bit positions here and in the other row walks: a lane's last one passes
-    // the row's end, which is at up to 2^31 - 1)
-    for (int64_t p = (int64_t)b + (threadIdx.x & 63); p < e; p += 64) rowid[p] = (int32_t)r;
+    // (unsigned or 64-bit positions here and in the other row walks: a lane's
+    // last one passes the row's end, which is at up to 2^31 - 1; unsigned ones
+    // cost nothing, 64-bit ones 1 of 72 us at 2 M entries)
+    const uint32_t end = (uint32_t)max(e, 0);
+    for (uint32_t p = (uint32_t)b + (threadIdx.x & 63); p < end; p += 64) rowid[p] = (int32_t)r;
 }
 
 // Symmetric pattern: A^T has A's row pointers and indices; the value at
