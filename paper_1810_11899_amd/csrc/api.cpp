@@ -556,7 +556,7 @@ static int layer_fwd(bool launch, const gcn_csr *A, const float *H, int32_t f_in
         if (af) {
             void *sw = ar.take<char>(pl.fwd_spmm);
             rc = spmm_bf16(n, A->nnz, A->indptr, idx_of(A), A->vals, H16, fp, fp, AGG16, fp,
-                           EPI_STORE_BF16, nullptr, sw, pl.fwd_spmm, s, bA);
+                           EPI_STORE_BF16, nullptr, sw, pl.fwd_spmm, s, bA, nullptr, 0, f_in);
             if (rc) return rc;
             if (!tnw && (rc = transpose_bf16(n, f_in, AGG16, 1, f_in, AGG16T, n, s))) return rc;
             g[1].seg[0] = GemmSeg{AGG16, fp, WnT, fp, fp};

@@ -149,11 +149,13 @@ int spmm_f32(int32_t n_rows, int32_t nnz, const int32_t *indptr, IdxRef indices,
              const float *vals, const float *X, int32_t k, int64_t ldx, void *out, int64_t ldo,
              int epilogue, const float *bias, void *ws, size_t ws_bytes, hipStream_t s,
              const int32_t *bounds = nullptr, uint16_t *out16 = nullptr, int64_t ld16 = 0);
-// same with bfloat16 rows of X (uint16 bits), float32 accumulation
+// same with bfloat16 rows of X (uint16 bits), float32 accumulation.  kv: columns
+// kv .. k - 1 are padding, and `out` holds zeros there whatever vals holds (one
+// output, not the accumulating or bias epilogue); 0: none.
 int spmm_bf16(int32_t n_rows, int32_t nnz, const int32_t *indptr, IdxRef indices,
               const float *vals, const uint16_t *X, int32_t k, int64_t ldx, void *out, int64_t ldo,
               int epilogue, const float *bias, void *ws, size_t ws_bytes, hipStream_t s,
-              const int32_t *bounds = nullptr, uint16_t *out16 = nullptr, int64_t ld16 = 0);
+              const int32_t *bounds = nullptr, uint16_t *out16 = nullptr, int64_t ld16 = 0, int32_t kv = 0);
 
 // GEMM on the matrix cores -----------------------------------------------------
 // C[M x N] = sum over up to two K-segments of op(A_s) op(B_s), then epilogue.

@@ -321,6 +321,16 @@ __device__ __forceinline__ void emit(void *__restrict__ out, int64_t ldo, int64_
     if (out16) store16<VEC, HWR>(out16 + r * ld16 + c, x, ovec);
 }
 
+// Sums of columns kv and on (a row's padding to whole vectors, whose X is zero)
+// become zero: an infinite matrix value times zero is NaN, which a product over
+// the padded row would spread over its outputs.
+template <int VEC>
+__device__ __forceinline__ void clear_padding(float (&acc)[VEC], int c, int32_t kv) {
+    if (c + VEC > kv)
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) acc[v] = c + v < kv ? acc[v] : 0.0f;
+}
+
 template <int VEC>
 __device__ __forceinline__ void store_raw(float *__restrict__ out, const float (&acc)[VEC]) {
 #pragma unroll
@@ -338,7 +348,8 @@ void spmm_main(
     const float *__restrict__ vals, const void *__restrict__ Xv, int32_t k, int64_t ldx,
     void *__restrict__ out, int64_t ldo, int epi, const float *__restrict__ bias, int ovec,
     int64_t items, int ipw, int64_t waves, const int32_t *__restrict__ bnd, float *__restrict__ carry,
-    int32_t *__restrict__ head_row, int32_t *__restrict__ tail_row, uint16_t *__restrict__ out16, int64_t ld16) {
+    int32_t *__restrict__ head_row, int32_t *__restrict__ tail_row, uint16_t *__restrict__ out16, int64_t ld16,
+    int32_t kv) {
     using Elem = typename std::conditional<BF16, uint16_t, float>::type;
     const Elem *__restrict__ X = (const Elem *)Xv;
     const int lane = threadIdx.x & 63;
@@ -414,6 +425,9 @@ void spmm_main(
                 }
         }
 
+        if constexpr (BF16 && OM == 0)
+#pragma unroll
+            for (int t = 0; t < CT; ++t) clear_padding<VEC>(acc[t], cbase + t * 64 * VEC, kv);
         const bool started = (r > r0) || (q0 == rb);
         if (complete && started) {
 #pragma unroll
@@ -584,7 +598,7 @@ void spmm_sliced_bf16(
     void *__restrict__ out, int64_t ldo, int epi, const float *__restrict__ bias,
     int64_t items, int ipw, int64_t waves, SliceMap map, const int32_t *__restrict__ bnd,
     float *__restrict__ carry, int32_t *__restrict__ head_row, int32_t *__restrict__ tail_row,
-    uint16_t *__restrict__ out16, int64_t ld16) {
+    uint16_t *__restrict__ out16, int64_t ld16, int32_t kv) {
     constexpr int LP = GCN_SPMM_BF16_LP;   // lanes per row piece
     constexpr int NG = 64 / LP;            // lane groups (edges per gather instruction)
     constexpr int SWD = 8 * LP;
@@ -662,6 +676,7 @@ void spmm_sliced_bf16(
         for (int o = LP; o < 64; o *= 2)
 #pragma unroll
             for (int v = 0; v < 8; ++v) a[v] += __shfl_xor(a[v], o);
+        if constexpr (OM == 0) clear_padding<8>(a, col, kv);
         const bool started = (r > r0) || (q0 == rb);
         if (g == 0 && cok) {
             if (complete && started) {
@@ -794,7 +809,8 @@ template <int VEC, int CT, bool BF16>
 void launch_main(dim3 grid, hipStream_t s, int32_t n_rows, const int32_t *indptr,
                  IdxRef indices, const float *vals, const void *X, int32_t k, int64_t ldx,
                  void *out, int64_t ldo, int epi, const float *bias, const SpmmPlan &pl,
-                 const int32_t *bnd, float *carry, int32_t *hr, int32_t *tr, uint16_t *out16, int64_t ld16) {
+                 const int32_t *bnd, float *carry, int32_t *hr, int32_t *tr, uint16_t *out16, int64_t ld16,
+                 int32_t kv) {
     // the epilogue's per-lane VEC outputs as one vector store when aligned
     const size_t chunk = std::min<size_t>(16, (size_t)VEC * (epi == EPI_STORE_BF16 ? 2 : 4));
     const size_t chunk16 = std::min<size_t>(16, (size_t)VEC * 2);
@@ -803,15 +819,15 @@ void launch_main(dim3 grid, hipStream_t s, int32_t n_rows, const int32_t *indptr
     if (out16 && out)
         hipLaunchKernelGGL((spmm_main<VEC, CT, BF16, 2>), grid, dim3(256), 0, s, n_rows, indptr, indices,
                            vals, X, k, ldx, out, ldo, epi, bias, ovec, pl.items, pl.ipw, pl.waves, bnd, carry, hr,
-                           tr, out16, ld16);
+                           tr, out16, ld16, kv);
     else if (out16)
         hipLaunchKernelGGL((spmm_main<VEC, CT, BF16, 1>), grid, dim3(256), 0, s, n_rows, indptr, indices,
                            vals, X, k, ldx, nullptr, ldo, epi, bias, ovec, pl.items, pl.ipw, pl.waves, bnd, carry,
-                           hr, tr, out16, ld16);
+                           hr, tr, out16, ld16, kv);
     else
         hipLaunchKernelGGL((spmm_main<VEC, CT, BF16, 0>), grid, dim3(256), 0, s, n_rows, indptr, indices,
                            vals, X, k, ldx, out, ldo, epi, bias, ovec, pl.items, pl.ipw, pl.waves, bnd, carry, hr,
-                           tr, nullptr, 0);
+                           tr, nullptr, 0, kv);
 }
 
 bool aligned(const void *p, int bytes) { return ((uintptr_t)p % (uintptr_t)bytes) == 0; }
@@ -819,7 +835,7 @@ bool aligned(const void *p, int bytes) { return ((uintptr_t)p % (uintptr_t)bytes
 int spmm_any(bool bf16, int32_t n_rows, int32_t nnz, const int32_t *indptr, IdxRef indices,
              const float *vals, const void *X, int32_t k, int64_t ldx, void *out, int64_t ldo,
              int epi, const float *bias, void *ws, size_t ws_bytes, hipStream_t s, const int32_t *bounds,
-             uint16_t *out16, int64_t ld16) {
+             uint16_t *out16, int64_t ld16, int32_t kv) {
     if (n_rows <= 0 || k <= 0) return GCN_OK;
     const SpmmPlan pl = spmm_plan(n_rows, nnz);
     Arena ar(ws, ws_bytes);
@@ -885,21 +901,21 @@ int spmm_any(bool bf16, int32_t n_rows, int32_t nnz, const int32_t *indptr, IdxR
             if (out16 && out)
                 hipLaunchKernelGGL(spmm_sliced_bf16<2>, g16, dim3(256), 0, s, n_rows, indptr, indices, vals, X16, k,
                                    ldx, out, ldo, epi, bias, pl.items, pl.ipw, pl.waves, m, bnd, carry, hr, tr, out16,
-                                   ld16);
+                                   ld16, kv);
             else if (out16)
                 hipLaunchKernelGGL(spmm_sliced_bf16<1>, g16, dim3(256), 0, s, n_rows, indptr, indices, vals, X16, k,
                                    ldx, nullptr, ldo, epi, bias, pl.items, pl.ipw, pl.waves, m, bnd, carry, hr, tr,
-                                   out16, ld16);
+                                   out16, ld16, kv);
             else
                 hipLaunchKernelGGL(spmm_sliced_bf16<0>, g16, dim3(256), 0, s, n_rows, indptr, indices, vals, X16, k,
                                    ldx, out, ldo, epi, bias, pl.items, pl.ipw, pl.waves, m, bnd, carry, hr, tr,
-                                   nullptr, 0);
+                                   nullptr, 0, kv);
             GCN_LAUNCH_CHECK("spmm_sliced_bf16");
         } else
 #define GCN_SPMM_CASE(V, C, B)                                                                   \
     if (vec == V && ct == C && bf16 == B) {                                                      \
         launch_main<V, C, B>(grid, s, n_rows, indptr, indices, vals, X, k, ldx, out, ldo, epi,   \
-                             bias, pl, bnd, carry, hr, tr, out16, ld16);                         \
+                             bias, pl, bnd, carry, hr, tr, out16, ld16, kv);                     \
     } else
         GCN_SPMM_CASE(4, 1, false)
         GCN_SPMM_CASE(4, 2, false)
@@ -974,15 +990,15 @@ int spmm_f32(int32_t n_rows, int32_t nnz, const int32_t *indptr, IdxRef indices,
              int epilogue, const float *bias, void *ws, size_t ws_bytes, hipStream_t s, const int32_t *bounds,
              uint16_t *out16, int64_t ld16) {
     return spmm_any(false, n_rows, nnz, indptr, indices, vals, X, k, ldx, out, ldo, epilogue, bias,
-                    ws, ws_bytes, s, bounds, out16, ld16);
+                    ws, ws_bytes, s, bounds, out16, ld16, k);
 }
 
 int spmm_bf16(int32_t n_rows, int32_t nnz, const int32_t *indptr, IdxRef indices,
               const float *vals, const uint16_t *X, int32_t k, int64_t ldx, void *out, int64_t ldo,
               int epilogue, const float *bias, void *ws, size_t ws_bytes, hipStream_t s, const int32_t *bounds,
-              uint16_t *out16, int64_t ld16) {
+              uint16_t *out16, int64_t ld16, int32_t kv) {
     return spmm_any(true, n_rows, nnz, indptr, indices, vals, X, k, ldx, out, ldo, epilogue, bias,
-                    ws, ws_bytes, s, bounds, out16, ld16);
+                    ws, ws_bytes, s, bounds, out16, ld16, kv > 0 ? kv : k);
 }
 
 }  // namespace gcn

@@ -1,12 +1,14 @@
 """bfloat16 layers whose widths and vertex counts are not multiples of the
 large-tile product's k-stage (32): padded input rows, K tails read as zeros,
 narrow weight gradients; against the oracle, forward and backward."""
+import numpy as np
 import pytest
 import torch
 
 import test_gpu_layer as TL
 from gpu_util import TOL_BF16, require_gpu
 from paper_1810_11899_amd import binding as B
+from paper_1810_11899_amd import synth
 
 pytestmark = pytest.mark.gpu
 
@@ -39,3 +41,24 @@ def test_ragged_layer(order, shape, ws):
 @pytest.mark.parametrize("n, f, C", [(1025, 264, 41), (4099, 128, 100), (1033, 68, 33), (2047, 1000, 31), (16385, 72, 5)])
 def test_ragged_head(kind, n, f, C, ws):
     TL.test_loss_grad(B.GCN_BF16, TOL_BF16, kind, n, f, C, ws)
+
+
+@pytest.mark.parametrize("f_in", [50, 203, 300, 602])     # padded to 56 (a column per lane), 208, 304, 608
+def test_infinite_matrix_values_stay_infinite(f_in, ws):
+    """An infinite value of A times the padding's zeros does not reach the
+    outputs: with positive features and weights they are infinite."""
+    n, h = 2000, 64
+    g = synth.custom(n, "rmat", 9, [(f_in, h)], seed=f_in).graph
+    deg = g.indptr[1:] - g.indptr[:-1]
+    rows = np.array([int(deg.argmax()), int(np.flatnonzero(deg == 3)[0])])   # cut over wavefronts, and short
+    vals = g.vals.copy()
+    vals[g.indptr[rows]] = np.inf
+    A = B.DeviceCSR.from_host(n, n, g.indptr, g.indices, vals)
+    gen = torch.Generator().manual_seed(f_in)
+    H, W = (torch.rand(s, generator=gen).add_(0.5).cuda() for s in ((n, f_in), (f_in, h)))
+    Y = torch.empty((n, 2 * h), device="cuda")
+    order = B.GCN_AGGREGATE_FIRST
+    saved = torch.empty(B.gcn_layer_saved_bytes(n, f_in, h, order, B.GCN_BF16), dtype=torch.uint8, device="cuda")
+    B.gcn_layer_fwd(A, H, W, W, torch.zeros(2 * h, device="cuda"), Y, saved, order, ws, B.GCN_BF16)
+    neigh = Y[:, h:].cpu().numpy()
+    assert np.isposinf(neigh[rows]).all() and np.isfinite(np.delete(neigh, rows, 0)).all()
