@@ -1389,36 +1389,64 @@ int bk_of(int mode) { return mode == 2 ? kBigBK : (mode == 1 || mode == 5 ? BK16
 int tile_m_of(int mode) { return mode == 2 ? kBigT : (mode == 1 ? kTBM16 : (mode == 3 ? 2 * kTBM : (mode >= 4 ? 64 : kTBM))); }
 int tile_n_of(int mode) { return mode == 2 ? kBigTN : (mode == 1 ? kTBN16 : (mode >= 4 ? 64 : kTBN)); }
 
+// a weight gradient on transposed copies: K (vertices) well past both sides
+bool long_k(const GemmProblem &g) { return (double)g.seg[0].K + g.seg[1].K > 4.0 * std::max(g.M, g.N); }
+
+// Whether 64 x 64 tiles take a bfloat16 product (bf16_mode): under 256 tiles of
+// 128 x 128, or a weight gradient of up to 2^29 multiply-adds.
+bool bf16_small(int layout, int nprob, const GemmProblem *probs) {
+    const double K = (double)probs[0].seg[0].K + probs[0].seg[1].K;
+    if (layout == L_TN || long_k(probs[0])) return (double)nprob * probs[0].M * probs[0].N * K <= (double)(1 << 29);
+    return (int64_t)nprob * ((probs[0].M + 127) / 128) * ((probs[0].N + 127) / 128) < 256;
+}
+
 // The large-tile bf16 kernel takes TN products of any K, and NT and NN
 // products whose K-segments are multiples of 8 (an operand with other widths
 // is kept with zero columns up to the next one), with 16-byte aligned operand rows; a k-major
 // operand (A of TN, B of TN and NN) is read in chunks of 8 along M (or N),
 // so its rows must hold M (N) rounded up to 8 (the extra columns only feed
 // outputs that are dropped).
-#ifndef GCN_BIG_NARROW_LO
-#define GCN_BIG_NARROW_LO 32
-#endif
-#ifndef GCN_BIG_NARROW_K
-#define GCN_BIG_NARROW_K 1024
-#endif
 bool big_ok(int layout, int nprob, const GemmProblem *probs) {
     if (GCN_BF16_BIG == 0) return false;
     const bool kma = layout == L_TN, kmb = layout != L_NT;
     for (int i = 0; i < nprob; ++i) {
         if (!GCN_BIG_MASKED && probs[i].mask16) return false;
-        // A side of 128 or less leaves most of a 256-wide tile idle.  Still
-        // worth it for a side of 64+ when the other one alone gives every CU
-        // a tile (the logits of a large subgraph): the product is then bound
-        // by its operand and output traffic, not by the idle matrix work.
-        // Also for a long-K product (a weight gradient over the subgraph's
-        // vertices), whose split-K blocks fill the GPU whatever the tiles, and
-        // which needs no transposed copies of its operands there: layer
-        // forward + backward, transposed copies / large tile, 8000 vertices
-        // 602 -> 128: 146 / 125 us, 3001 vertices 50 -> 64: 79 / 66 us.
+        // A side of 128 or less leaves most of a 256-wide tile idle.
         const int lo = min(probs[i].M, probs[i].N);
         const int64_t tiles = (int64_t)((probs[i].M + kBigT - 1) / kBigT) * ((probs[i].N + kBigTN - 1) / kBigTN);
         const int64_t K = (int64_t)probs[i].seg[0].K + probs[i].seg[1].K;
-        if (lo <= 128 && !(lo >= GCN_BIG_NARROW_LO && (tiles >= GCN_BIG_NARROW_TILES || K >= GCN_BIG_NARROW_K))) return false;
+        if (layout == L_TN) {
+            // A weight gradient's split-K blocks fill the GPU whatever the
+            // tiles, and it needs no transposed copies of its operands here.
+            // Layer forward + backward, transposed copies / large tile: 8000
+            // vertices 602 -> 128 146 / 125 us, 3001 vertices 50 -> 64 79 / 66;
+            // 65,536 vertices 602 -> 32 397 / 240, 200 -> 56 191 / 179, 50 -> 40
+            // 145 / 144.  (The forward pass wins; the backward call by itself is
+            // up to a fifth slower there with a side under 64: 110 / 97, 99 / 96,
+            // 59 / 56.)
+            if (lo <= 128 && !(lo >= 32 && (tiles >= GCN_BIG_NARROW_TILES || K >= 1024))) return false;
+        } else {
+            // Where 64 x 64 tiles are taken (bf16_small) they are faster: forward
+            // 200 -> 256, 8000 vertices 46 / 53 us (9286 x 300, past the rule: on
+            // 128 x 128 tiles 68 / 64), 16,138 x 300 -> 64 43 / 55, 2120 x 300 ->
+            // 284 backward 30 / 38.  (A masked product stays here, where its mask
+            // is read 8 bytes at a time.)
+            const bool masked = probs[i].mask16 != nullptr;
+            if (!masked && bf16_small(layout, nprob, probs)) return false;
+            // Narrow: one round of blocks, and then the product is bound by its
+            // operand and output traffic, not by the idle matrix work (bfloat16
+            // heads, 128 x 128 tiles / large: 41 classes, 33,000 x 256 104 / 98,
+            // 65,536 x 1024 298 / 285; but 80,000 x 256 (313 blocks) 162 / 168;
+            // layers, two products a launch: 200 -> 64 forward, 25,000 vertices
+            // 58.2 / 57.4, 33,000 (258 blocks) 64 / 77, 65,536 91 / 104; 32
+            // columns lose everywhere: 20,000 x 200 50 / 55).  Never a weight
+            // gradient on transposed copies (1024 x 60 over 20,000: 70 / 87).
+            if (lo <= 128 && !(lo > 32 && tiles * nprob <= 256 && !long_k(probs[0]))) return false;
+            // Rows of N not a multiple of 4 are stored element by element, which
+            // short products do not hide (dH of 602 -> h, 30,000 vertices: K = 2h
+            // = 32 103 / 116, 128 122 / 134, 192 131 / 143).
+            if (!masked && lo > 128 && probs[i].N % 4 && K <= 192) return false;
+        }
         for (int s = 0; s < 2; ++s) {
             const GemmSeg &sg = probs[i].seg[s];
             if (sg.K == 0) continue;
@@ -1482,14 +1510,12 @@ int f32_mode(int layout, int nprob, const GemmProblem *probs, int &split_k) {
 // / 64 x 64: sigmoid head, 16,000 vertices 103 / 90 us; 50 -> 64 forward, 3001
 // vertices 43 / 32 us; 200 -> 64 backward, 1000 vertices 56 / 53 us.
 int bf16_mode(int layout, int nprob, const GemmProblem *probs, int &split_k) {
-    auto tiles = [&](int t) { return (int64_t)nprob * ((probs[0].M + t - 1) / t) * ((probs[0].N + t - 1) / t); };
     for (int i = 0; i < nprob; ++i)
         if (probs[i].colpart) return 1;
-    const int64_t t64 = tiles(64);
-    const double K = (double)probs[0].seg[0].K + probs[0].seg[1].K;
-    const bool long_k = layout == L_TN || K > 4.0 * std::max(probs[0].M, probs[0].N);
-    if (long_k ? (double)nprob * probs[0].M * probs[0].N * K > (double)(1 << 29) : tiles(128) >= 256) return 1;
-    const int64_t most = !long_k && t64 >= 256 ? 1 : std::max<int64_t>(1, 512 / t64);
+    if (!bf16_small(layout, nprob, probs)) return 1;
+    const int64_t t64 = (int64_t)nprob * ((probs[0].M + 63) / 64) * ((probs[0].N + 63) / 64);
+    const bool lk = layout == L_TN || long_k(probs[0]);
+    const int64_t most = !lk && t64 >= 256 ? 1 : std::max<int64_t>(1, 512 / t64);
     split_k = (int)std::min<int64_t>(split_k, most);
     return 5;
 }

@@ -62,3 +62,18 @@ def test_infinite_matrix_values_stay_infinite(f_in, ws):
     B.gcn_layer_fwd(A, H, W, W, torch.zeros(2 * h, device="cuda"), Y, saved, order, ws, B.GCN_BF16)
     neigh = Y[:, h:].cpu().numpy()
     assert np.isposinf(neigh[rows]).all() and np.isfinite(np.delete(neigh, rows, 0)).all()
+
+
+# both sides of the large tile's rules for forward and input-gradient products:
+# one head launch of 127 / 129 blocks of 256 rows, 32 / 33 classes; two products
+# a launch of 126 / 130 blocks; 78 / 80 blocks of wide ones; rows of N mod 4
+@pytest.mark.parametrize("n, f, C", [(32512, 64, 33), (33024, 64, 32), (33024, 64, 33), (33000, 64, 41)])
+def test_head_at_the_large_tile_rules(n, f, C, ws):
+    TL.test_loss_grad(B.GCN_BF16, TOL_BF16, "ce", n, f, C, ws)
+
+
+@pytest.mark.parametrize("shape", [(16128, "er", 4, 72, 40), (16640, "er", 4, 72, 40), (9984, "er", 4, 56, 136),
+                                   (10240, "er", 4, 56, 136), (20500, "er", 4, 130, 8), (20500, "er", 4, 134, 104)])
+def test_layer_at_the_large_tile_rules(shape, ws):
+    TL.test_layer_forward(B.GCN_BF16, TOL_BF16, B.GCN_AGGREGATE_FIRST, shape, ws)
+    TL.test_layer_backward(B.GCN_BF16, TOL_BF16, B.GCN_AGGREGATE_FIRST, True, shape, ws)
