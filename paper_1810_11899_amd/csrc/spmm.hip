@@ -426,8 +426,9 @@ void spmm_main(
         }
 
         if constexpr (BF16 && OM == 0)
+            if (kv < k)
 #pragma unroll
-            for (int t = 0; t < CT; ++t) clear_padding<VEC>(acc[t], cbase + t * 64 * VEC, kv);
+                for (int t = 0; t < CT; ++t) clear_padding<VEC>(acc[t], cbase + t * 64 * VEC, kv);
         const bool started = (r > r0) || (q0 == rb);
         if (complete && started) {
 #pragma unroll
@@ -590,7 +591,10 @@ void spmm_sliced(
 // columns there are two slices, each on four XCDs, whose L2s then hold
 // 512-byte pieces of twice as many hot rows as whole 1 KB rows would allow.
 // OM selects the epilogue's outputs as in spmm_main.
-template <int OM>
+// PAD (OM 0, EPI_STORE_BF16): columns kv and on are cleared (clear_padding), a
+// whole row's by masks on its packed words: cleared as floats in every row, the
+// 200- to 600-wide gathers of 2000 vertices took 1.5 of 15 us longer.
+template <int OM, bool PAD>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GCN_SPMM_BF16_WPE)))
 void spmm_sliced_bf16(
     int32_t n_rows, const int32_t *__restrict__ indptr, IdxRef indices,
@@ -626,6 +630,11 @@ void spmm_sliced_bf16(
     const int col = slice * SWD + (lane % LP) * 8;
     const bool cok = col < k;
     constexpr int U = GCN_SPMM_BF16_U;
+    uint32_t keep[4];   // PAD: the packed words' bits of columns before kv
+    if constexpr (PAD)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            keep[q] = (col + 2 * q < kv ? 0xFFFFu : 0u) | (col + 2 * q + 1 < kv ? 0xFFFF0000u : 0u);
 
     const int q0 = (int)p0;
     int32_t hrow = -1, trow = -1;
@@ -676,13 +685,18 @@ void spmm_sliced_bf16(
         for (int o = LP; o < 64; o *= 2)
 #pragma unroll
             for (int v = 0; v < 8; ++v) a[v] += __shfl_xor(a[v], o);
-        if constexpr (OM == 0) clear_padding<8>(a, col, kv);
         const bool started = (r > r0) || (q0 == rb);
         if (g == 0 && cok) {
-            if (complete && started) {
+            if (PAD && complete && started) {
+                uint4 w = make_uint4(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(a[4], a[5]),
+                                     pack_bf16x2(a[6], a[7]));
+                w.x &= keep[0]; w.y &= keep[1]; w.z &= keep[2]; w.w &= keep[3];
+                *(uint4 *)((uint16_t *)out + r * ldo + col) = w;
+            } else if (complete && started) {
                 emit<8, OM, OM != 2>(out, ldo, r, col, a, epi, bias_s + (lane % LP) * 8, true, out16, ld16);   // aligned (host checks; the pair rounding where it fits the registers)
             } else if (complete || pe > pb) {
                 const int slot = complete ? 0 : 1;
+                if constexpr (PAD) clear_padding<8>(a, col, kv);
                 store_raw<8>(carry + (2 * wave + slot) * (int64_t)k + col, a);
             }
         }
@@ -899,15 +913,19 @@ int spmm_any(bool bf16, int32_t n_rows, int32_t nnz, const int32_t *indptr, IdxR
             const dim3 g16((unsigned)slice_map_blocks(m));
             const uint16_t *X16 = (const uint16_t *)X;
             if (out16 && out)
-                hipLaunchKernelGGL(spmm_sliced_bf16<2>, g16, dim3(256), 0, s, n_rows, indptr, indices, vals, X16, k,
+                hipLaunchKernelGGL((spmm_sliced_bf16<2, false>), g16, dim3(256), 0, s, n_rows, indptr, indices, vals, X16, k,
                                    ldx, out, ldo, epi, bias, pl.items, pl.ipw, pl.waves, m, bnd, carry, hr, tr, out16,
                                    ld16, kv);
             else if (out16)
-                hipLaunchKernelGGL(spmm_sliced_bf16<1>, g16, dim3(256), 0, s, n_rows, indptr, indices, vals, X16, k,
+                hipLaunchKernelGGL((spmm_sliced_bf16<1, false>), g16, dim3(256), 0, s, n_rows, indptr, indices, vals, X16, k,
                                    ldx, nullptr, ldo, epi, bias, pl.items, pl.ipw, pl.waves, m, bnd, carry, hr, tr,
                                    out16, ld16, kv);
+            else if (kv < k && epi == EPI_STORE_BF16)
+                hipLaunchKernelGGL((spmm_sliced_bf16<0, true>), g16, dim3(256), 0, s, n_rows, indptr, indices, vals, X16,
+                                   k, ldx, out, ldo, epi, bias, pl.items, pl.ipw, pl.waves, m, bnd, carry, hr, tr,
+                                   nullptr, 0, kv);
             else
-                hipLaunchKernelGGL(spmm_sliced_bf16<0>, g16, dim3(256), 0, s, n_rows, indptr, indices, vals, X16, k,
+                hipLaunchKernelGGL((spmm_sliced_bf16<0, false>), g16, dim3(256), 0, s, n_rows, indptr, indices, vals, X16, k,
                                    ldx, out, ldo, epi, bias, pl.items, pl.ipw, pl.waves, m, bnd, carry, hr, tr,
                                    nullptr, 0, kv);
             GCN_LAUNCH_CHECK("spmm_sliced_bf16");
