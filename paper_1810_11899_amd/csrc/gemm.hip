@@ -1509,12 +1509,22 @@ int f32_mode(int layout, int nprob, const GemmProblem *probs, int &split_k) {
 // NT on transposed copies) of up to 2^29 multiply-adds.  Whole calls, 128 x 128
 // / 64 x 64: sigmoid head, 16,000 vertices 103 / 90 us; 50 -> 64 forward, 3001
 // vertices 43 / 32 us; 200 -> 64 backward, 1000 vertices 56 / 53 us.
-int bf16_mode(int layout, int nprob, const GemmProblem *probs, int &split_k) {
+// Operands read element by element (not vec) are read twice as often by the
+// small tiles unless a side fits one of them; past some work (whole tiles
+// counted) that outweighs the fuller GPU.  Backward, 128 x 128 / 64 x 64: 3073
+// vertices 602 -> 73 (5.0e8 of work) 56 / 63 us, 9722 200 -> 97 66 / 74, 6342 300
+// -> 65 83 / 87; but 3195 200 -> 231 (4.2e8) 109 / 98, 4689 200 -> 101 40 / 38,
+// and one tile of 64 wide 23,783 300 -> 34 135 / 121.  Forward 3533 602 -> 315
+// (1.4e9) 87 / 99; but 2490 292 -> 446 (6.5e8) 79 / 72.
+int bf16_mode(int layout, int nprob, const GemmProblem *probs, bool vec, int &split_k) {
     for (int i = 0; i < nprob; ++i)
         if (probs[i].colpart) return 1;
     if (!bf16_small(layout, nprob, probs)) return 1;
     const int64_t t64 = (int64_t)nprob * ((probs[0].M + 63) / 64) * ((probs[0].N + 63) / 64);
+    const int64_t t128 = (int64_t)nprob * ((probs[0].M + 127) / 128) * ((probs[0].N + 127) / 128);
     const bool lk = layout == L_TN || long_k(probs[0]);
+    const double work = 4096.0 * t64 * ((double)probs[0].seg[0].K + probs[0].seg[1].K);
+    if (!vec && t64 > 3 * t128 && work > (lk ? 7 : 12) * (double)(1 << 26)) return 1;
     const int64_t most = !lk && t64 >= 256 ? 1 : std::max<int64_t>(1, 512 / t64);
     split_k = (int)std::min<int64_t>(split_k, most);
     return 5;
@@ -1686,7 +1696,7 @@ int gemm(int layout, int nprob, const GemmProblem *probs, int bf16, int split_k,
     }
     DevArgs a;
     int64_t blocks = 0;
-    const int mode = big ? 2 : (bf16 ? bf16_mode(layout, nprob, probs, split_k) : f32_mode(layout, nprob, probs, split_k));
+    const int mode = big ? 2 : (bf16 ? bf16_mode(layout, nprob, probs, vec, split_k) : f32_mode(layout, nprob, probs, split_k));
     fill_dev(layout, nprob, probs, mode, split_k, partial, a, blocks);
     if (blocks == 0) return GCN_OK;
     if (nprob == 2 && (a.p[0].kt_total != a.p[1].kt_total || a.p[0].split != a.p[1].split)) {

@@ -77,3 +77,13 @@ def test_head_at_the_large_tile_rules(n, f, C, ws):
 def test_layer_at_the_large_tile_rules(shape, ws):
     TL.test_layer_forward(B.GCN_BF16, TOL_BF16, B.GCN_AGGREGATE_FIRST, shape, ws)
     TL.test_layer_backward(B.GCN_BF16, TOL_BF16, B.GCN_AGGREGATE_FIRST, True, shape, ws)
+
+
+# operands read element by element on both sides of the 64 x 64 tiles' rule:
+# weight gradients of 4.4, 4.8 and (one tile wide) 6.2e8 multiply-adds in whole
+# tiles, forward and input-gradient products of 7.8 and 8.3e8
+@pytest.mark.parametrize("shape", [(4203, "er", 4, 202, 201), (4603, "er", 4, 202, 201), (15001, "er", 4, 301, 61),
+                                   (1985, "er", 4, 602, 301), (2115, "er", 4, 602, 301)])
+def test_elementwise_operands_at_the_tile_rule(shape, ws):
+    TL.test_layer_forward(B.GCN_BF16, TOL_BF16, B.GCN_AGGREGATE_FIRST, shape, ws)
+    TL.test_layer_backward(B.GCN_BF16, TOL_BF16, B.GCN_TRANSFORM_FIRST, True, shape, ws)
