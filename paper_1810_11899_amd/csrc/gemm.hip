@@ -1393,10 +1393,10 @@ int tile_n_of(int mode) { return mode == 2 ? kBigTN : (mode == 1 ? kTBN16 : (mod
 bool long_k(const GemmProblem &g) { return (double)g.seg[0].K + g.seg[1].K > 4.0 * std::max(g.M, g.N); }
 
 // Whether 64 x 64 tiles take a bfloat16 product (bf16_mode): under 256 tiles of
-// 128 x 128, or a weight gradient of up to 2^29 multiply-adds.
+// 128 x 128, or a weight gradient of up to 2^30 multiply-adds.
 bool bf16_small(int layout, int nprob, const GemmProblem *probs) {
     const double K = (double)probs[0].seg[0].K + probs[0].seg[1].K;
-    if (layout == L_TN || long_k(probs[0])) return (double)nprob * probs[0].M * probs[0].N * K <= (double)(1 << 29);
+    if (layout == L_TN || long_k(probs[0])) return (double)nprob * probs[0].M * probs[0].N * K <= (double)(1 << 30);
     return (int64_t)nprob * ((probs[0].M + 127) / 128) * ((probs[0].N + 127) / 128) < 256;
 }
 
@@ -1477,9 +1477,12 @@ bool big_ok(int layout, int nprob, const GemmProblem *probs) {
 //     (Column sums are kept per 128 rows and need a taller tile.)
 //   - Weight gradients (TN, K = vertices): 64 x 64 tiles and a fourth of the
 //     splits while the product is small enough for their second read of the
-//     operands not to matter: 2^29 multiply-adds (8000 x 256 x 128 both
-//     branches, the layer's backward pass 77 / 74 us; 6205 x 256 x 41, the
-//     head 53 / 45 us; but 8000 x 602 x 128 69 / 74, 16,000 x 300 x 256 75 / 90).
+//     operands not to matter: 2^30 multiply-adds.  Backward passes, time on 128 x
+//     128 tiles over time on 64 x 64, geometric mean of 12 pairs of widths from
+//     50 x 64 to 600 x 300: 1.30 at 2^27, 1.27 at 2^28, 1.20 at 2^29, 1.16 at
+//     2^29.5, 1.13 at 2^30 (1.05 over the six widest, 0.96 to 1.11), 1.02 at
+//     2^30.5 (0.90 to 1.08 there), 0.97 at 2^31 (0.86 to 1.06).  Narrower than 64
+//     they stay ahead, by 1.1 at 2^31 (600 x 60).
 //     Above that two blocks per CU of few tiles: four, as for many, only add
 //     partials (300 x 256 over 16,000 vertices 88 / 75 us).
 int f32_mode(int layout, int nprob, const GemmProblem *probs, int &split_k) {
@@ -1492,7 +1495,7 @@ int f32_mode(int layout, int nprob, const GemmProblem *probs, int &split_k) {
     auto at_most = [&](int64_t n) { split_k = (int)std::min<int64_t>(split_k, std::max<int64_t>(1, n)); };
     if (layout == L_TN) {
         const double madds = (double)nprob * probs[0].M * probs[0].N * ((double)probs[0].seg[0].K + probs[0].seg[1].K);
-        if (!colpart && madds <= (double)(1 << 29)) {
+        if (!colpart && madds <= (double)(1 << 30)) {
             at_most(512 / t64);
             return 4;
         }
@@ -1506,8 +1509,9 @@ int f32_mode(int layout, int nprob, const GemmProblem *probs, int &split_k) {
 
 // The bfloat16 kernel's tile, by the same reasoning: 64 x 64 for products of
 // under 256 tiles of 128 x 128, and for weight gradients (K = vertices, TN or
-// NT on transposed copies) of up to 2^29 multiply-adds.  Whole calls, 128 x 128
-// / 64 x 64: sigmoid head, 16,000 vertices 103 / 90 us; 50 -> 64 forward, 3001
+// NT on transposed copies) of up to 2^30 multiply-adds (backward on transposed
+// copies, 128 x 128 over 64 x 64, mean of 12 widths: 1.10 at 2^28 and 2^29, 1.07
+// at 2^30, 1.02 at 2^30.5, 0.95 at 2^31).  Whole calls, 128 x 128 / 64 x 64: sigmoid head, 16,000 vertices 103 / 90 us; 50 -> 64 forward, 3001
 // vertices 43 / 32 us; 200 -> 64 backward, 1000 vertices 56 / 53 us.
 // Operands read element by element (not vec) are read twice as often by the
 // small tiles unless a side fits one of them; past some work (whole tiles

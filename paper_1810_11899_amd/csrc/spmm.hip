@@ -885,8 +885,10 @@ int spmm_any(bool bf16, int32_t n_rows, int32_t nnz, const int32_t *indptr, IdxR
                         aligned(out, 16) && k >= 128 && (!out16 || (ld16 % 4 == 0 && aligned(out16, 8)));
     // bfloat16 rows on the sliced schedule: whole 8-column lane vectors and
     // 16-byte aligned rows in and out, wide enough for two edges per gather to
-    // beat one with a lane per column or two (layer calls, whole: k = 200 at
-    // 50,000 vertices 220 / 185 us, k = 128 at 20,000 80 / 75 us unsliced / sliced)
+    // beat one with a lane per column or two.  Whole layer calls, unsliced /
+    // sliced, k = 72 to 248 over 2000 to 65,536 vertices: 1.01 to 1.15 at 15 edges
+    // a row and 1.05 to 1.6 at 40 (k = 200 at 50,000 vertices 220 / 185 us), with
+    // 5 edges a row 1.01 to 1.05, the accumulating epilogue 0.97 to 1.00.
     const bool sliced16 = GCN_SPMM_BF16_SLICED && bf16 && k > 64 && k % 8 == 0 && ldx % 8 == 0 &&
                           aligned(X, 16) && (!out || (ldo % 8 == 0 && aligned(out, 16))) &&
                           (!out16 || (ld16 % 8 == 0 && aligned(out16, 16)));
