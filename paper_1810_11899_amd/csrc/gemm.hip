@@ -157,11 +157,14 @@ typedef float float4a4 __attribute__((ext_vector_type(4), aligned(4)));   // 16-
 constexpr int kBK = 16;           // K depth of one LDS stage
 constexpr int64_t kFastLd = 1 << 22;   // leading dimensions whose tile offsets fit 32 bits
 
-constexpr float kSplitScale = 0x1p24f, kSumScale = 0x1p-48f;
-// x0, x1 -> the packed h, m and l parts of kSplitScale times them
+constexpr int kSplitScaleLog2 = 24;
+constexpr float kSumScale = 0x1p-48f;
+// x0, x1 -> the packed h, m and l parts of 2^kSplitScaleLog2 times them
 __device__ __forceinline__ void split3(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l) {
-    x0 *= kSplitScale;
-    x1 *= kSplitScale;
+    // (ldexp: a multiplication would be fused into the subtractions below, which
+    // need it as a literal operand of a longer instruction)
+    x0 = __builtin_amdgcn_ldexpf(x0, kSplitScaleLog2);
+    x1 = __builtin_amdgcn_ldexpf(x1, kSplitScaleLog2);
     h = pack_bf16x2(x0, x1);
     const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xFFFF0000u);
     m = pack_bf16x2(r0, r1);
@@ -1476,15 +1479,17 @@ bool big_ok(int layout, int nprob, const GemmProblem *probs) {
 //     forward over 8000 vertices 50 / 43 us, 200 -> 128 over 700 38 / 28 us.
 //     (Column sums are kept per 128 rows and need a taller tile.)
 //   - Weight gradients (TN, K = vertices): 64 x 64 tiles and a fourth of the
-//     splits while the product is small enough for their second read of the
-//     operands not to matter: 2^30 multiply-adds.  Backward passes, time on 128 x
-//     128 tiles over time on 64 x 64, geometric mean of 12 pairs of widths from
-//     50 x 64 to 600 x 300: 1.30 at 2^27, 1.27 at 2^28, 1.20 at 2^29, 1.16 at
-//     2^29.5, 1.13 at 2^30 (1.05 over the six widest, 0.96 to 1.11), 1.02 at
-//     2^30.5 (0.90 to 1.08 there), 0.97 at 2^31 (0.86 to 1.06).  Narrower than 64
-//     they stay ahead, by 1.1 at 2^31 (600 x 60).
+//     splits while their second read of the operands does not matter: up to 2^30
+//     multiply-adds, with up to 16 of them, or with one side in a single tile.
+//     Backward passes, time on 128 x 128 tiles over time on 64 x 64, geometric
+//     mean of 12 pairs of widths from 50 x 64 to 600 x 300: 1.30 at 2^27, 1.20 at
+//     2^29, 1.13 at 2^30, 1.02 at 2^30.5, 0.97 at 2^31.  128 x 128 (8 tiles) 1.38 at
+//     2^30, 1.43 at 2^31; 256 x 128 (16) 1.08 at 2^31, 0.98 at 2^32; 1000 x 64 1.12 at
+//     2^31, 1.01 at 2^33; but 300 x 100 (20) 0.91 at 2^32, 602 x 128 (40) 0.76.
 //     Above that two blocks per CU of few tiles: four, as for many, only add
 //     partials (300 x 256 over 16,000 vertices 88 / 75 us).
+//   - 256 x 128 only where it adds no rows of padding: 96 x 512 over 65,536
+//     vertices 338 / 292 us (256 / 128 rows), 602 x 512 879 / 802.
 int f32_mode(int layout, int nprob, const GemmProblem *probs, int &split_k) {
     auto tiles = [&](int tm, int tn) {
         return (int64_t)nprob * ((probs[0].M + tm - 1) / tm) * ((probs[0].N + tn - 1) / tn);
@@ -1495,7 +1500,7 @@ int f32_mode(int layout, int nprob, const GemmProblem *probs, int &split_k) {
     auto at_most = [&](int64_t n) { split_k = (int)std::min<int64_t>(split_k, std::max<int64_t>(1, n)); };
     if (layout == L_TN) {
         const double madds = (double)nprob * probs[0].M * probs[0].N * ((double)probs[0].seg[0].K + probs[0].seg[1].K);
-        if (!colpart && madds <= (double)(1 << 30)) {
+        if (!colpart && (t64 <= 16 || t64 <= 2 * t128 || madds <= (double)(1 << 30))) {
             at_most(512 / t64);
             return 4;
         }
@@ -1504,7 +1509,8 @@ int f32_mode(int layout, int nprob, const GemmProblem *probs, int &split_k) {
         at_most(t64 >= 256 ? 1 : 512 / t64);
         return 4;
     }
-    return tiles(2 * kTBM, kTBN) * std::max(1, split_k) >= 512 ? 3 : 0;
+    const int64_t t256 = tiles(2 * kTBM, kTBN);
+    return t256 * std::max(1, split_k) >= 512 && 2 * t256 <= t128 ? 3 : 0;
 }
 
 // The bfloat16 kernel's tile, by the same reasoning: 64 x 64 for products of

@@ -159,3 +159,17 @@ def test_shortest_sums(K):
     if K == 1:    # the input gradient: K = 2h = 2, the other half's term zero
         _, _, _, dH = run(np.ones((3000, 160), np.float32), np.ascontiguousarray(Bm.T), A)
         shortest(dH, A, Bm)
+
+
+# weight gradients on both sides of the 64 x 64 tiles' rules (2^30 multiply-adds,
+# 16 tiles, one side in a tile) and of the 256-row tile's (no rows of padding)
+@pytest.mark.parametrize("n, f, h", [(11000, 320, 140), (12000, 320, 150), (70000, 128, 128), (70000, 129, 128),
+                                     (30000, 320, 64), (70000, 256, 300), (70000, 257, 300)])
+def test_weight_gradients_at_the_tile_rules(n, f, h):
+    rg = np.random.default_rng(n + f)
+    H, dY = rg.standard_normal((n, f), dtype=np.float32), rg.standard_normal((n, h), dtype=np.float32)
+    _, _, dW, _ = run(H, np.zeros((f, h), np.float32), dY)
+    ref = H.T.astype(np.float64) @ dY.astype(np.float64)
+    # 128 or fewer splits of k-tiles: at most 3 n / 16 roundings of sums that grow
+    # as sqrt(n); 2-norm error below 4e-7 at every n (the float32 cores': 6e-7)
+    assert np.linalg.norm(dW - ref) <= 4e-7 * np.linalg.norm(ref)
