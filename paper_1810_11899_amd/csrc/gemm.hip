@@ -1478,9 +1478,10 @@ bool big_ok(int layout, int nprob, const GemmProblem *probs) {
 //     and no reduce pass.  Whole calls, 128 x 128 split / 64 x 64: 256 -> 128
 //     forward over 8000 vertices 50 / 43 us, 200 -> 128 over 700 38 / 28 us.
 //     (Column sums are kept per 128 rows and need a taller tile.)
-//   - Weight gradients (TN, K = vertices): 64 x 64 tiles and a fourth of the
-//     splits while their second read of the operands does not matter: up to 2^30
-//     multiply-adds, with up to 16 of them, or with one side in a single tile.
+//   - Weight gradients (TN, K = vertices): 64 x 64 tiles while their second read
+//     of the operands does not matter: up to 2^30 multiply-adds, with up to 16 of
+//     them, or with one side in a single tile.  A fourth of the splits up to 2^29;
+//     past that fewer would make the sums longer than the larger tiles' were.
 //     Backward passes, time on 128 x 128 tiles over time on 64 x 64, geometric
 //     mean of 12 pairs of widths from 50 x 64 to 600 x 300: 1.30 at 2^27, 1.20 at
 //     2^29, 1.13 at 2^30, 1.02 at 2^30.5, 0.97 at 2^31.  128 x 128 (8 tiles) 1.38 at
@@ -1500,11 +1501,10 @@ int f32_mode(int layout, int nprob, const GemmProblem *probs, int &split_k) {
     auto at_most = [&](int64_t n) { split_k = (int)std::min<int64_t>(split_k, std::max<int64_t>(1, n)); };
     if (layout == L_TN) {
         const double madds = (double)nprob * probs[0].M * probs[0].N * ((double)probs[0].seg[0].K + probs[0].seg[1].K);
-        if (!colpart && (t64 <= 16 || t64 <= 2 * t128 || madds <= (double)(1 << 30))) {
-            at_most(512 / t64);
-            return 4;
-        }
-        if (t128 < 32) at_most(512 / t128);
+        const bool small = !colpart && (t64 <= 16 || t64 <= 2 * t128 || madds <= (double)(1 << 30));
+        if (small && madds <= (double)(1 << 29)) at_most(512 / t64);
+        else if (t128 < 32) at_most(512 / t128);
+        if (small) return 4;
     } else if (!colpart && t128 < 256) {
         at_most(t64 >= 256 ? 1 : 512 / t64);
         return 4;
@@ -1536,7 +1536,9 @@ int bf16_mode(int layout, int nprob, const GemmProblem *probs, bool vec, int &sp
     const double work = 4096.0 * t64 * ((double)probs[0].seg[0].K + probs[0].seg[1].K);
     if (!vec && t64 > 3 * t128 && work > (lk ? 7 : 12) * (double)(1 << 26)) return 1;
     const int64_t most = !lk && t64 >= 256 ? 1 : std::max<int64_t>(1, 512 / t64);
-    split_k = (int)std::min<int64_t>(split_k, most);
+    // (weight gradients past 2^29 keep their splits: no longer sums)
+    if (!lk || (double)nprob * probs[0].M * probs[0].N * ((double)probs[0].seg[0].K + probs[0].seg[1].K) <= (double)(1 << 29))
+        split_k = (int)std::min<int64_t>(split_k, most);
     return 5;
 }
 
