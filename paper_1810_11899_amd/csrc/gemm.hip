@@ -96,8 +96,10 @@ __device__ __forceinline__ bool decode_block(const DevArgs &a, BlockCoord &c) {
 }
 
 // ------------------------------------------------------------- float32 kernel
-// float32 products on the bfloat16 matrix cores.  Every operand element x is
-// split exactly into three bfloat16 parts, x = h + m + l: h = rne(x),
+// float32 products on the bfloat16 matrix cores, by splitting the operands (the
+// method of Henry, Tang and Heinecke, "Leveraging the bfloat16 artificial
+// intelligence datatype for higher-precision computations", 2019).  Every operand
+// element x is split exactly into three bfloat16 parts, x = h + m + l: h = rne(x),
 // m = rne(x - h), l = x - h - m (8 significant bits each; the differences are
 // exact in float32), and a product accumulates the six part products
 // h h', h m', m h', m m', h l', l h' in float32.  The parts left out (m l',
@@ -125,11 +127,11 @@ __device__ __forceinline__ bool decode_block(const DevArgs &a, BlockCoord &c) {
 // 4.9 / 4.4, 5.9 / 5.1.
 //
 // Why: the bfloat16 cores do 16 times the float32 cores' rate, so six
-// products leave 2.7 times the float32 peak.  Measured at 65,536 vertices
-// (float32 cores before / now): 1024 -> 512 both branches, NT 1054 / 711 us,
-// TN 1044 / 651 us; NN 512 and 1024 -> 512 on average 824 / 565 us per launch,
-// i.e. 1.2 PFLOP/s of bfloat16 work: the clock falls to 1.9 GHz under it
-// (2.4 on zero operands), with the matrix cores busy 62% of the cycles.
+// products leave 2.7 times the float32 peak.  Measured at 65,536 vertices (the
+// 2-layer step of 512-wide features, 512 and 512 hidden units, 100 classes;
+// TFLOP/s on the float32 cores / now): NN 123 / 181, TN 127 / 204, NT 119 / 163,
+// i.e. 1.09, 1.22 and 0.98 PFLOP/s of bfloat16 work, with the matrix cores busy
+// 51%, 58% and 44% of the cycles at about 2.1 GHz (cycles over launch times).
 //
 // Range: unscaled, the parts of an element below 2^-109 fall under the
 // smallest bfloat16, and nothing in the sums tells it (such an element times a
@@ -142,14 +144,22 @@ __device__ __forceinline__ bool decode_block(const DevArgs &a, BlockCoord &c) {
 // a sum that is not finite is computed again, unscaled, on the float32 cores
 // before the epilogue and gives what float32 products give.  (So an element of
 // a block can take either path, and differ in its last bits, by what another
-// row of the block holds; the block costs the second pass too.)
+// row of the block holds; the block costs the second pass too: a 512 -> 512
+// forward layer over 65,536 vertices 470 us, 482 with an infinity in one row,
+// 950 with one in every block.)
+// The scaling costs 2% of a float32 call on average and 1% of that step (4.58 ->
+// 4.63 ms); backward passes over 65,536 vertices on few 128 x 128 tiles lose most
+// (384 -> 128 181 -> 208 us, 300 -> 100 170 -> 196).  (The remainders by
+// v_dot2_f32_bf16, 9 instructions a pair instead of 13, are slower: the step 4.56
+// -> 4.74 ms.)
 //
 // LDS: per operand and k-tile of 16, three planes (h, m, l) of two chunks
 // (k 0-7, k 8-15) of XT rows x 16 bytes, so that a fragment read (8
 // consecutive k of 32 consecutive rows per half-wavefront) is contiguous;
 // the chunks lie 128 bytes past a multiple of 256 apart, so that the 8-byte
-// stores of an operand contiguous along k (four lanes per row) fall in
-// distinct banks.  Two buffers, one barrier per k-tile: while a tile is
+// stores of an operand contiguous along k (four lanes per row) spread over the
+// banks (counted all the same, per LDS instruction: 1.3 conflict cycles in NN,
+// 1.8 in NT, none in TN, which has no such operand).  Two buffers, one barrier per k-tile: while a tile is
 // multiplied, the next one is split and stored to the other buffer, and the
 // one after it is loaded to registers.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));

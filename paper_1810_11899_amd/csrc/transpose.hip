@@ -360,8 +360,9 @@ SortPlan sort_plan(int32_t n_cols, int32_t nnz) {
     SortPlan p;
     const int bits = std::max(1, key_bits(n_cols));
     p.ntiles = (int32_t)(((int64_t)nnz + kTile - 1) / kTile);
-    // a single tile counts at most 256 digits: a workspace of no more than 16
-    // bytes an entry and 3 KB also for a few entries
+    // a single tile counts at most 256 digits, which keeps its workspace to 16
+    // bytes an entry and 3 KB (more tiles: 2 KB each of 4096 entries on top, and
+    // the digits' totals)
     const int most = p.ntiles == 1 ? 8 : kDigitBits;
     p.passes = (bits + most - 1) / most;
     p.dbits = (bits + p.passes - 1) / p.passes;
